@@ -19,7 +19,7 @@ OUT = os.path.join(PKG, "liblbm.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 
 # the longest compiles first, so that the parallel build ends together
-SOURCES = ["lbm_mrt_3d_q19_flow_fp.hip", "lbm_mrt_3d_q19_flow_16.hip", "lbm_mrt_3d_q19.hip", "lbm_gk_3d.hip",
+SOURCES = ["lbm_mrt_2d_q9.hip", "lbm_mrt_3d_q19_flow_fp.hip", "lbm_mrt_3d_q19_flow_16.hip", "lbm_mrt_3d_q19.hip", "lbm_gk_3d.hip",
            "lbm_trt_3d.hip", "lbm_mrt_2d.hip", "lbm_paper_3d.hip", "lbm_3d.hip", "lbm_2d.hip", "lbm_trt_2d.hip",
            "lbm_gk_2d.hip", "lbm_vd_3d.hip", "lbm_mrt_3d.hip", "lbm_paper_2d.hip", "lbm_vd_2d.hip", "lbm_api.hip",
            "probe.hip", "lbm_nc3_3d.hip", "lbm_nc3_2d.hip"]

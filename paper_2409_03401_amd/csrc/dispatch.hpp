@@ -26,6 +26,10 @@ struct KernelSet {
     // adjoint to (set = false) or from (set = true) an FP64 [slot][node] array
     void (*adj_copy)(const KParams& kp, int nslots, long long nodes, double* buf, bool set, hipStream_t s);
     int tx, ty;  // work-group tile of the fused kernel
+    // several steps per launch on windows of nt nodes (2D; nullptr: no such kernel);
+    // block_nt: the small and the large window
+    void (*block)(int nt, unsigned grid, const KParams& kp, const BlockGeom& g, hipStream_t s);
+    int block_nt[2];
 };
 
 // fluid: 0 (none) or 9 / 19; prec: Prec; (tx, ty): work-group tile, 0 for the

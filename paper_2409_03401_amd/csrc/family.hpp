@@ -3,6 +3,7 @@
 // storage precisions.
 #pragma once
 
+#include "block2d.hpp"
 #include "dispatch.hpp"
 #include "kernels.hpp"
 
@@ -82,10 +83,24 @@ struct Family {
             else hipLaunchKernelGGL((k_adj_copy<SL, FL, false>), grid, dim3(256), 0, s, kp, nodes, buf);
         }
     }
+    // the narrow row segments (LBM_TILE) march one step per launch
+    static constexpr bool kBlock = SL::DIM == 2 && TX == 256;
+    static constexpr int kSmall = 256;
+    static constexpr int large() {
+        if constexpr (kBlock) return block_threads<SL, FL, PREC, COLL, NC>();
+        else return 0;
+    }
+    static void block(int nt, unsigned grid, const KParams& kp, const BlockGeom& g, hipStream_t s) {
+        if constexpr (kBlock) {
+            if (nt == kSmall) hipLaunchKernelGGL((k_block<SL, FL, PREC, kSmall, COLL, NC>), dim3(grid), dim3(kSmall), 0, s, kp, g);
+            else hipLaunchKernelGGL((k_block<SL, FL, PREC, large(), COLL, NC>), dim3(grid), dim3(large()), 0, s, kp, g);
+        }
+    }
     static constexpr KernelSet set{&fused, &init, &get_pops, &set_pops, &walls,
                                    kAdj ? &adj_step : nullptr, kAdj ? &adj_seed : nullptr,
                                    kAdj ? &adj_gather : nullptr, kAdj ? &adj_init_local : nullptr,
-                                   kAdj ? &adj_copy : nullptr, TX, TY};
+                                   kAdj ? &adj_copy : nullptr, TX, TY,
+                                   kBlock ? &block : nullptr, {kBlock ? kSmall : 0, large()}};
 };
 
 template <class SL, class FL, int TX, int TY>

@@ -16,7 +16,8 @@
 // X_k(x) whose source x - e_k lies beyond a z wall is read from the node's own slot
 // opp(k) instead (zbounce).  Every reader of a state (step, moments, initialisation,
 // population access, adjoint) follows this rule.  Walls on x and y are a small fix-up
-// kernel after the step (k_walls).
+// kernel after the step (k_walls).  2D runs of several steps go through k_block
+// (block2d.hpp); the update of a node itself is in node.hpp.
 //
 // Memory layout of one copy: a sequence of slots, one [node] array per
 // (field, direction) in the canonical order f_0.., g_0.., hA_0.., hB_0...  Every
@@ -24,305 +25,9 @@
 // offset, so each load / store is one `global_* voffset, saddr` instruction.
 #pragma once
 
-#include <cstddef>
-#include <type_traits>
-
-#include "adjoint.hpp"
-#include "lattice.hpp"
-#include "params.hpp"
-#include "physics.hpp"
+#include "node.hpp"
 
 namespace lbm {
-
-// ---------------------------------------------------------------------------
-// helpers
-
-
-
-// 1/x: exact in FP64, the hardware reciprocal (1 ulp) in FP32
-template <class C>
-__device__ __forceinline__ C rcp(C x) {
-    if constexpr (std::is_same<C, double>::value) return 1.0 / x;
-    else return __builtin_amdgcn_rcpf(x);
-}
-
-// Work-groups are handed to the 8 XCDs of the chip round-robin by linear id.
-// Remap so that XCD j owns the contiguous range of tiles [j N / 8, (j + 1) N / 8):
-// tiles that share phi-halo cache lines then run on the same XCD and meet in
-// its L2 instead of each fetching the lines from memory.
-__device__ __forceinline__ int xcd_tile(int w, int n) {
-    constexpr int kXcd = 8;
-    const int base = n / kXcd, rem = n % kXcd;
-    const int j = w % kXcd, local = w / kXcd;
-    return j < rem ? j * (base + 1) + local : rem * (base + 1) + (j - rem) * base + local;
-}
-
-// periodic wrap / mirror ghost of a coordinate in [-1, n]
-__device__ __forceinline__ int map_coord(int c, int n, int wall) {
-    if (c < 0) return wall ? 0 : n - 1;
-    if (c >= n) return wall ? n - 1 : 0;
-    return c;
-}
-
-// index offsets of the six axis neighbours of node (x, y, z), periodic wrap folded in
-struct Nbr {
-    int xp, xm, yp, ym, zp, zm;
-};
-
-__device__ __forceinline__ Nbr neighbours(int x, int y, int z, const KParams& P) {
-    const int nxny = P.nx * P.ny;
-    Nbr n;
-    n.xp = (x + 1 < P.nx) ? 1 : 1 - P.nx;
-    n.xm = (x > 0) ? -1 : P.nx - 1;
-    n.yp = (y + 1 < P.ny) ? P.nx : (1 - P.ny) * P.nx;
-    n.ym = (y > 0) ? -P.nx : (P.ny - 1) * P.nx;
-    n.zp = (z + 1 < P.nz) ? nxny : (1 - P.nz) * nxny;
-    n.zm = (z > 0) ? -nxny : (P.nz - 1) * nxny;
-    return n;
-}
-
-// offset of the node x - e that a population moving along e arrives from (pull)
-template <int EX, int EY, int EZ>
-__device__ __forceinline__ int pull_offset(const Nbr& n) {
-    int d = 0;
-    if constexpr (EX > 0) d += n.xm;
-    if constexpr (EX < 0) d += n.xp;
-    if constexpr (EY > 0) d += n.ym;
-    if constexpr (EY < 0) d += n.yp;
-    if constexpr (EZ > 0) d += n.zm;
-    if constexpr (EZ < 0) d += n.zp;
-    return d;
-}
-
-// A 32-bit byte offset the optimiser may not widen to 64 bits (an empty asm with a
-// register operand, no instruction).  Base (SGPR) + this offset selects the
-// `global_* voffset, saddr` form instead of a 64-bit per-lane address.
-__device__ __forceinline__ unsigned voff(unsigned byte_offset) {
-    asm("" : "+v"(byte_offset));
-    return byte_offset;
-}
-
-// index offsets of the axis neighbours for the phi stencil: periodic wrap, or the
-// node itself beyond a wall (mirror ghost of a half-way wall)
-__device__ __forceinline__ Nbr stencil_neighbours(int x, int y, int z, const KParams& P) {
-    const int nxny = P.nx * P.ny;
-    Nbr n;
-    n.xp = (x + 1 < P.nx) ? 1 : (P.wall_x ? 0 : 1 - P.nx);
-    n.xm = (x > 0) ? -1 : (P.wall_x ? 0 : P.nx - 1);
-    n.yp = (y + 1 < P.ny) ? P.nx : (P.wall_y ? 0 : (1 - P.ny) * P.nx);
-    n.ym = (y > 0) ? -P.nx : (P.wall_y ? 0 : (P.ny - 1) * P.nx);
-    n.zp = (z + 1 < P.nz) ? nxny : (P.wall_z ? 0 : (1 - P.nz) * nxny);
-    n.zm = (z > 0) ? -nxny : (P.wall_z ? 0 : (P.nz - 1) * nxny);
-    return n;
-}
-
-// offset of the node x + e
-template <int EX, int EY, int EZ>
-__device__ __forceinline__ int push_offset(const Nbr& n) {
-    return pull_offset<-EX, -EY, -EZ>(n);
-}
-
-// does the pull of a population moving along z-component EZ at a node on the low
-// (zlo) or high (zhi) z wall plane cross the wall?  Then it bounces back: the node's
-// own population of the opposite direction (Section 4.2.4, half-way bounce-back).
-template <int EZ>
-__device__ __forceinline__ bool zbounce(bool zlo, bool zhi) {
-    if constexpr (EZ > 0) return zlo;
-    else if constexpr (EZ < 0) return zhi;
-    else return false;
-}
-
-// ---------------------------------------------------------------------------
-// population storage
-
-// slot bookkeeping of one lattice family: f, g, then NC composition fields (hA, hB,
-// and hC with three compositions); rest slots (k = 0) are f_0, g_0, hA_0, hB_0 (, hC_0)
-template <int QF, int QS, int NC = 2>
-struct Slots {
-    static constexpr int G0 = QF, A0 = QF + QS, B0 = QF + 2 * QS, C0 = QF + 3 * QS, N = QF + (1 + NC) * QS;
-    __host__ __device__ static constexpr bool rest(int s) {
-        return (QF > 0 && s == 0) || s == G0 || s == A0 || s == B0 || (NC >= 3 && s == C0);
-    }
-    __host__ __device__ static constexpr int rest_before(int s) {
-        return (QF > 0 && s > 0 ? 1 : 0) + (s > G0 ? 1 : 0) + (s > A0 ? 1 : 0) + (s > B0 ? 1 : 0) +
-               (NC >= 3 && s > C0 ? 1 : 0);
-    }
-    __host__ __device__ static constexpr int field(int s) {
-        return s < G0 ? 0 : (s < A0 ? 1 : (s < B0 ? 2 : (s < C0 ? 3 : 4)));
-    }
-};
-
-// byte offset of slot S in a copy (moving slots take stride_m bytes, rest slots stride_r)
-template <class SLOTS, int S>
-__device__ __forceinline__ unsigned long long slot_offset(const KParams& P) {
-    constexpr int rb = SLOTS::rest_before(S);
-    return (unsigned long long)(S - rb) * P.stride_m + (unsigned long long)rb * P.stride_r;
-}
-
-// where a reader finds X_k(x) (slot S = direction k of lattice L of a field): slot S at
-// the pull source x - e_k, or the node's own slot of opp(k) when that crosses a z wall
-// (zbounce).  Returns the slot base in `base`'s copy and the node index in t.
-template <class SLOTS, class L, int S, int K>
-__device__ __forceinline__ const char* pull_src(const char* base, const KParams& P, int z, unsigned idx,
-                                                const Nbr& nb, unsigned& t) {
-    if (zbounce<L::ez(K)>(P.wall_z && z == 0, P.wall_z && z == P.nz - 1)) {
-        t = idx;
-        return base + slot_offset<SLOTS, S - K + L::opp(K)>(P);
-    }
-    t = unsigned(int(idx) + pull_offset<L::ex(K), L::ey(K), L::ez(K)>(nb));
-    return base + slot_offset<SLOTS, S>(P);
-}
-
-// load one population at node idx and decode it to the compute type
-// NT: a non-temporal load, for data no other work-group reads
-template <class T, bool NT>
-__device__ __forceinline__ T ld_raw(const T* p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
-
-template <int PREC, bool REST, bool NT = false>
-__device__ __forceinline__ typename Stor<PREC>::C ld_at(const char* slot, unsigned idx, float wref,
-                                                        float inv_scale) {
-    if constexpr (PREC == P64) {
-        return ld_raw<double, NT>(reinterpret_cast<const double*>(slot + idx * 8u));
-    } else if constexpr (PREC == P32 || REST) {
-        return ld_raw<float, NT>(reinterpret_cast<const float*>(slot + idx * 4u));
-    } else {
-        const unsigned short bits = ld_raw<unsigned short, NT>(reinterpret_cast<const unsigned short*>(slot + idx * 2u));
-        if constexpr (PREC == P16) return fmaf(__half2float(__ushort_as_half(bits)), inv_scale, wref);
-        else return float(__builtin_bit_cast(__bf16, bits)) + wref;  // BF16: no scale
-    }
-}
-
-// decode the low / high 16 bits of a word as a moving 16-bit population (the words of
-// the packed LDS ring); the same arithmetic as ld_at
-template <int PREC>
-__device__ __forceinline__ float dec_lo(unsigned w, float wref, float inv_scale) {
-    if constexpr (PREC == P16) return fmaf(__half2float(__ushort_as_half((unsigned short)(w & 0xffffu))), inv_scale, wref);
-    else return __builtin_bit_cast(float, w << 16) + wref;
-}
-template <int PREC>
-__device__ __forceinline__ float dec_hi(unsigned w, float wref, float inv_scale) {
-    if constexpr (PREC == P16) return fmaf(__half2float(__ushort_as_half((unsigned short)(w >> 16))), inv_scale, wref);
-    else return __builtin_bit_cast(float, w & 0xffff0000u) + wref;
-}
-
-// 16-bit encoding of one moving population: d = (v - w_k ref) 2^s in FP16, or v - w_k ref
-// in BF16 (its exponent range is FP32's, so it takes no scale), rounded to nearest even
-template <int PREC>
-__device__ __forceinline__ float enc_d(float v, float wref, float scale) {
-    if constexpr (PREC == P16) return (v - wref) * scale;
-    else return v - wref;
-}
-
-// encode and store one population; populations written by a step are read again
-// only in the next step, so they stream past the caches (non-temporal stores)
-template <int PREC, bool REST>
-__device__ __forceinline__ void st_at(char* slot, unsigned idx, float wref, float scale,
-                                      typename Stor<PREC>::C v) {
-    if constexpr (PREC == P64) {
-        __builtin_nontemporal_store(v, reinterpret_cast<double*>(slot + idx * 8u));
-    } else if constexpr (PREC == P32 || REST) {
-        __builtin_nontemporal_store(float(v), reinterpret_cast<float*>(slot + idx * 4u));
-    } else {
-        const float d = enc_d<PREC>(v, wref, scale);
-        unsigned short bits;
-        if constexpr (PREC == P16) bits = __half_as_ushort(__float2half_rn(d));
-        else bits = __builtin_bit_cast(unsigned short, __bf16(d));  // round to nearest even
-        __builtin_nontemporal_store(bits, reinterpret_cast<unsigned short*>(slot + idx * 2u));
-    }
-}
-
-// store, returning the value the slot now decodes to (16-bit moving populations:
-// the rounded value; otherwise v itself)
-template <int PREC, bool REST>
-__device__ __forceinline__ typename Stor<PREC>::C st_at_r(char* slot, unsigned idx, float wref, float scale,
-                                                           float inv_scale, typename Stor<PREC>::C v) {
-    if constexpr (PREC == P64 || PREC == P32 || REST) {
-        st_at<PREC, REST>(slot, idx, wref, scale, v);
-        return v;
-    } else {
-        const float d = enc_d<PREC>(v, wref, scale);
-        unsigned short bits;
-        float back;
-        if constexpr (PREC == P16) {
-            const __half hd = __float2half_rn(d);
-            bits = __half_as_ushort(hd);
-            back = __half2float(hd) * inv_scale;
-        } else {
-            const __bf16 bd = __bf16(d);  // round to nearest even
-            bits = __builtin_bit_cast(unsigned short, bd);
-            back = float(bd);
-        }
-        __builtin_nontemporal_store(bits, reinterpret_cast<unsigned short*>(slot + idx * 2u));
-        return back + wref;
-    }
-}
-
-// store a moving 16-bit population and return its rounding residue in the encoded
-// domain, d - round(d); (value - stored value) is that times 2^-s (FP16) or itself (BF16)
-template <int PREC>
-__device__ __forceinline__ float st_at_res(char* slot, unsigned idx, float wref, float scale, float v) {
-    static_assert(PREC == P16 || PREC == PB16, "16-bit formats only");
-    const float d = enc_d<PREC>(v, wref, scale);
-    unsigned short bits;
-    float back;
-    if constexpr (PREC == P16) {
-        const __half hd = __float2half_rn(d);
-        bits = __half_as_ushort(hd);
-        back = __half2float(hd);
-    } else {
-        const __bf16 bd = __bf16(d);  // round to nearest even
-        bits = __builtin_bit_cast(unsigned short, bd);
-        back = float(bd);
-    }
-    __builtin_nontemporal_store(bits, reinterpret_cast<unsigned short*>(slot + idx * 2u));
-    return d - back;
-}
-
-// store two moving 16-bit populations of one field (slots sa, sb at node idx, the same
-// reference w_k ref) with one packed conversion (round to nearest even); returns the sum
-// of their stored deviations in the encoded domain
-template <int PREC>
-__device__ __forceinline__ float st2_at_dev(char* sa, char* sb, unsigned idx, float wref, float scale, float va,
-                                            float vb) {
-    static_assert(PREC == P16 || PREC == PB16, "16-bit formats only");
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 d = {enc_d<PREC>(va, wref, scale), enc_d<PREC>(vb, wref, scale)};
-    unsigned bits;
-    float back;
-    if constexpr (PREC == P16) {
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        const h2 r = __builtin_convertvector(d, h2);
-        bits = __builtin_bit_cast(unsigned, r);
-        back = float(r.x) + float(r.y);
-    } else {
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        bits = __builtin_bit_cast(unsigned, __builtin_convertvector(d, b2));
-        back = __builtin_bit_cast(float, bits << 16) + __builtin_bit_cast(float, bits & 0xffff0000u);
-    }
-    __builtin_nontemporal_store((unsigned short)(bits & 0xffffu), reinterpret_cast<unsigned short*>(sa + idx * 2u));
-    __builtin_nontemporal_store((unsigned short)(bits >> 16), reinterpret_cast<unsigned short*>(sb + idx * 2u));
-    return back;
-}
-
-// runtime-slot variants (generic copy kernels)
-template <int PREC>
-__device__ __forceinline__ typename Stor<PREC>::C ld_pop(const void* base, int idx, bool rest,
-                                                         float wref, float inv_scale) {
-    const char* p = static_cast<const char*>(base);
-    if (rest) return ld_at<PREC, true>(p, unsigned(idx), wref, inv_scale);
-    return ld_at<PREC, false>(p, unsigned(idx), wref, inv_scale);
-}
-
-template <int PREC>
-__device__ __forceinline__ void st_pop(void* base, int idx, bool rest, float wref, float scale,
-                                       typename Stor<PREC>::C v) {
-    char* p = static_cast<char*>(base);
-    if (rest) st_at<PREC, true>(p, unsigned(idx), wref, scale, v);
-    else st_at<PREC, false>(p, unsigned(idx), wref, scale, v);
-}
 
 // ---------------------------------------------------------------------------
 // block reduction of N doubles (entry `maxslot` takes a max, the others a sum),
@@ -382,72 +87,12 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[N], int maxslot, 
 #ifndef LBM_NT_FLUID
 #define LBM_NT_FLUID 1
 #endif
-#ifndef LBM_PHASES
-#define LBM_PHASES 0
-#endif
 #ifndef LBM_FLAT_FILL
 #define LBM_FLAT_FILL 1
 #endif
 #ifndef LBM_FRAW
 #define LBM_FRAW 1
 #endif
-
-// scheduling fence between phases of the collision (bounds register live ranges)
-#define LBM_FENCE()                                          \
-    do {                                                     \
-        if constexpr (LBM_PHASES) __builtin_amdgcn_sched_barrier(0); \
-    } while (0)
-
-// index of the pair (k, opp(k)), k < opp(k), among the moving directions of lattice L
-template <class L, int K>
-constexpr int pair_index() {
-    int n = 0;
-    for (int j = 1; j < K; ++j)
-        if (j < L::opp(j)) ++n;
-    return n;
-}
-
-// MRT relaxation of one field (the multiple-relaxation-time alternative to BGK):
-// n_k = X_k - eqs(k) to the moment basis, moment i times rate(i) / <M_i, M_i>, back
-// with M^-1_{k i} = w_k M_ik / <M_i, M_i>, then out(k, X_k - w_k (M^T m)_k + src(k)).
-template <class L>
-inline constexpr MomentBasis<L::Q> kBasis = make_moment_basis<L>();
-
-template <class L, class C, class EQ, class SRC, class RATE, class OUT>
-__device__ __forceinline__ void mrt_relax(const C (&X)[L::Q], EQ&& eqs, SRC&& src, RATE&& rate, OUT&& out) {
-    constexpr int Q = L::Q;
-    C n[Q], m[Q];
-    static_for<0, Q>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        n[k] = X[k] - eqs(kc);
-    });
-    static_for<0, Q>([&](auto ic) __attribute__((always_inline)) {
-        constexpr int i = decltype(ic)::value;
-        C a = C(0);
-        static_for<0, Q>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value;
-            constexpr double mik = kBasis<L>.M[i][k];
-            if constexpr (mik != 0.0) a += C(mik) * n[k];
-        });
-        m[i] = a * (rate(ic) * C(kBasis<L>.invD[i]));
-    });
-    static_for<0, Q>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        C a = C(0);
-        static_for<0, Q>([&](auto ic) __attribute__((always_inline)) {
-            constexpr int i = decltype(ic)::value;
-            constexpr double mik = kBasis<L>.M[i][k];
-            if constexpr (mik != 0.0) a += C(mik) * m[i];
-        });
-        out(kc, X[k] - C(L::w(k)) * a + src(kc));
-    });
-}
-
-// order of row i of the basis, and whether it is the trace of the second order
-template <class L, int I>
-constexpr int basis_order() { return kBasis<L>.order[I]; }
-template <class L, int I>
-constexpr bool basis_trace() { return kBasis<L>.order[I] == 2 && (I == 0 || kBasis<L>.order[I - 1] != 2); }
 
 // occupancy floor of the fused kernel: one wave per SIMD (the compiler may use every
 // register), except where a higher floor measured faster at 256^3:
@@ -494,7 +139,8 @@ k_lbm(const KParams P) {
     constexpr bool FLOW = QF > 0;
     constexpr bool STENCIL = FLOW || MODE == MODE_DIAG;
     constexpr bool HAS_Y = SL::DIM == 3;
-    using STL = typename std::conditional<SL::DIM == 2, D2Q9K, D3Q19K>::type;
+    using NODE = Node<SL, FL, PREC, COLL, NC>;
+    using STL = typename NODE::STL;
     constexpr int LX = TX + 2;
     constexpr int LY = HAS_Y ? TY + 2 : 1;
     constexpr int OY = HAS_Y ? 1 : 0;
@@ -506,11 +152,8 @@ k_lbm(const KParams P) {
     constexpr int QC = NC3 ? QS : 1;
     static_assert(NC == 2 || (NC == 3 && COLL == COLL_BGK), "a third composition runs with the BGK Boussinesq step");
     static_assert(SLOTS::N <= kMaxSlots, "slot table too small for this lattice family");
-    constexpr C inv_cs2s = C(1.0 / SL::cs2);
-    constexpr bool TRTC = (COLL & COLL_TRT) != 0;
-    constexpr bool MRTC = (COLL & COLL_MRT) != 0;
-    constexpr bool VD = FLOW && (COLL & COLL_VD) != 0;
-    constexpr bool GK = (COLL & COLL_GK) != 0;
+    constexpr bool VD = NODE::VD;
+    constexpr bool GK = NODE::GK;
     static_assert(TY == 1 || HAS_Y, "2D problems use one row per work-group");
     // the private LDS ring of scalar populations, unless it would not leave room for a
     // second work-group per compute unit (the paper's D3Q19 scalar lattice in FP32 / FP64,
@@ -579,26 +222,8 @@ k_lbm(const KParams P) {
         const unsigned long long b = reinterpret_cast<kslot*>(kargs + offsetof(KParams, dst_slot))[S];
         return (char*)(gmut*)b;
     };
-    // 16-bit reference w_k ref_field of slot S (direction k of lattice L): zero for the
-    // compositions (their moving equilibria w_k mu are near zero) and for f in BF16 (its
-    // deviations need no scale, and f ~ w_k p_h is centred on zero)
-    constexpr bool NOREF_F = PREC == PB16;
-    auto wref = [&](auto s_, auto k_, auto lat_) __attribute__((always_inline)) -> float {
-        using L = typename decltype(lat_)::type;
-        constexpr int F = SLOTS::field(decltype(s_)::value);
-        if constexpr (F >= 2 || (F == 0 && NOREF_F)) return 0.0f;
-        else return float(L::w(decltype(k_)::value)) * P.fref[F];
-    };
-    // the reference a decode adds: a zero reference as -0.0, since x + (-0.0) = x folds away
-    // (x + 0.0 does not: it maps -0.0 to +0.0) and the encode's x - 0.0 folds as well
     auto wref_dec = [&](auto s_, auto k_, auto lat_) __attribute__((always_inline)) -> float {
-        constexpr int F = SLOTS::field(decltype(s_)::value);
-        if constexpr (F >= 2 || (F == 0 && NOREF_F)) return -0.0f;
-        else return wref(s_, k_, lat_);
-    };
-    auto load = [&](auto s_, auto k_, auto lat_, unsigned idx) __attribute__((always_inline)) -> C {
-        constexpr int S = decltype(s_)::value;
-        return ld_at<PREC, SLOTS::rest(S)>(src(s_), idx, wref_dec(s_, k_, lat_), P.finv[SLOTS::field(S)]);
+        return NODE::wref_dec(P, s_, k_, lat_);
     };
     // fluid populations that arrive without an x shift are read by this work-group
     // only (no ring, no x neighbour shares their lines): streamed past the caches.
@@ -609,44 +234,6 @@ k_lbm(const KParams P) {
         constexpr bool NT = LBM_NT_FLUID && SL::DIM == 3 && L::ex(decltype(k_)::value) == 0;
         return ld_at<PREC, SLOTS::rest(S), NT>(src(s_), idx, wref_dec(s_, k_, lat_), P.finv[SLOTS::field(S)]);
     };
-    auto store = [&](auto s_, auto k_, auto lat_, unsigned idx, C v) __attribute__((always_inline)) {
-        constexpr int S = decltype(s_)::value;
-        st_at<PREC, SLOTS::rest(S)>(dst(s_), idx, wref(s_, k_, lat_), P.fscale[SLOTS::field(S)], v);
-    };
-    // store a 16-bit moving population and add its rounding residue, in the encoded
-    // domain, to res; fb<F>(res) is the residue in values of field F
-    auto store_r = [&](auto s_, auto k_, auto lat_, unsigned idx, C v, C& res) __attribute__((always_inline)) {
-        constexpr int S = decltype(s_)::value;
-        static_assert(!SLOTS::rest(S), "rest populations carry no residue");
-        res += st_at_res<PREC>(dst(s_), idx, wref(s_, k_, lat_), P.fscale[SLOTS::field(S)], v);
-    };
-    auto fb = [&](auto f_, C res) __attribute__((always_inline)) -> C {
-        if constexpr (PREC == P16) return res * P.finv[decltype(f_)::value];
-        else return res;
-    };
-    // sum of the stored moving populations of field F on lattice L, from the sum of their
-    // stored deviations: sum_{k != 0} w_k ref_F + dev 2^-s
-    auto stored_sum = [&](auto f_, auto lat_, C dev) __attribute__((always_inline)) -> C {
-        using L = typename decltype(lat_)::type;
-        constexpr int F = decltype(f_)::value;
-        if constexpr (F >= 2 || (F == 0 && NOREF_F)) return fb(f_, dev);
-        else return fb(f_, dev) + C(1.0 - L::w(0)) * P.fref[F];
-    };
-
-    // FP32 sum of the moving populations of one field, in the order k1, opp(k1), k2,
-    // opp(k2), ... over k < opp(k) (16-bit storage; the packed LDS fill sums in this order)
-    auto moving_sum = [&](const auto& x) __attribute__((always_inline)) -> C {
-        C m = C(0);
-        static_for<1, QS>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value, o = SL::opp(k);
-            if constexpr (k < o) {
-                if constexpr (pair_index<SL, k>() == 0) m = x[k] + x[o];
-                else m = (m + x[k]) + x[o];
-            }
-        });
-        return m;
-    };
-
     // scalar populations arriving at node idx (pull from idx - e_k; the node's own
     // opposite population where that crosses a z wall: zlo / zhi, wave-uniform)
     // The scalar populations of a node in their stored form (RAW: 16-bit storage keeps
@@ -692,46 +279,18 @@ k_lbm(const KParams P) {
         decode_field(IC<B0>{}, raw + 2 * QS, bb);
         if constexpr (NC3) decode_field(IC<HC0>{}, raw + 3 * QS, qq);
     };
-    auto pop_sums = [&](const C (&gg)[QS], const C (&aa)[QS], const C (&bb)[QS], const C (&qq)[QC], double& phis,
-                        double& cA, double& cB, double& cC) __attribute__((always_inline)) {
-        // zeroth moments.  mu = c - c^eq(phi) cancels c ~ 0.3 down to ~1e-3, so FP32
-        // partial sums over all populations (several roundings of c and phi each) would
-        // enter mu with a relative error near 1e-4 per step: FP32 / FP64 storage sums in
-        // FP64.  16-bit storage sums its moving populations in FP32 and adds the FP32
-        // rest population in FP64: the moving h are ~w_k mu (their FP32 sum is near
-        // exact) and the moving g carry 16-bit storage noise far above FP32 rounding
-        if constexpr (PREC == P16 || PREC == PB16) {
-            phis = double(gg[0]) + double(moving_sum(gg));
-            cA = double(aa[0]) + double(moving_sum(aa));
-            cB = double(bb[0]) + double(moving_sum(bb));
-            cC = NC3 ? double(qq[0]) + double(moving_sum(qq)) : 0.0;
-        } else {
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-#pragma unroll
-            for (int k = 0; k < QS; ++k) {
-                s0 += double(gg[k]);
-                s1 += double(aa[k]);
-                s2 += double(bb[k]);
-                if constexpr (NC3) s3 += double(qq[k]);
-            }
-            phis = s0;
-            cA = s1;
-            cB = s2;
-            cC = s3;
-        }
-    };
     auto load_scalars = [&](unsigned idx, const Nbr& nb, bool zlo, bool zhi, C (&gg)[QS], C (&aa)[QS],
                             C (&bb)[QS], C (&qq)[QC], double& phis, double& cA, double& cB, double& cC)
                             __attribute__((always_inline)) {
         RW raw[NSC];
         load_pops(idx, nb, zlo, zhi, raw);
         decode_pops(raw, gg, aa, bb, qq);
-        pop_sums(gg, aa, bb, qq, phis, cA, cB, cC);
+        NODE::pop_sums(gg, aa, bb, qq, phis, cA, cB, cC);
     };
     // phi of a node from its population sums (Eqs. Moment0_Phi, PotChem)
     auto phi_from = [&](double ps, double sa, double sb, double sc) __attribute__((always_inline)) -> double {
-        if constexpr (NC3) return node_scalars3(ps, sa, sb, sc, P).phi;
-        else return node_scalars<GK>(ps, sa, sb, P).phi;
+        double muC;
+        return NODE::scalars(ps, sa, sb, sc, P, muC).phi;
     };
 
     auto node_phi = [&](int xx, int yy, int zz, bool zlo, bool zhi) __attribute__((always_inline)) -> C {
@@ -828,10 +387,10 @@ k_lbm(const KParams P) {
                 spop[pbuf][2 * QS + k][tid] = bb[k];
                 if constexpr (NC3) spop[pbuf][3 * QS + k][tid] = qq[k];
             }
-            pop_sums(gg, aa, bb, qq, ps, cA, cB, cC);
+            NODE::pop_sums(gg, aa, bb, qq, ps, cA, cB, cC);
         } else {
             decode_pops(own, ng, na, nb, nq);
-            pop_sums(ng, na, nb, nq, ps, cA, cB, cC);
+            NODE::pop_sums(ng, na, nb, nq, ps, cA, cB, cC);
         }
         sphi[slot][ty + OY][tx + 1] = C(phi_from(ps, cA, cB, cC));
         // the first lane of this wave holds a ring node (wave-uniform)
@@ -839,7 +398,7 @@ k_lbm(const KParams P) {
             C tg[QS], ta[QS], tb[QS], tq[QC];
             double rps, rsa, rsb, rsc;
             decode_pops(ring, tg, ta, tb, tq);
-            pop_sums(tg, ta, tb, tq, rps, rsa, rsb, rsc);
+            NODE::pop_sums(tg, ta, tb, tq, rps, rsa, rsb, rsc);
             sphi[slot][hy][hx] = C(phi_from(rps, rsa, rsb, rsc));
         }
     };
@@ -948,11 +507,6 @@ k_lbm(const KParams P) {
     for (int i = 0; i < NACC; ++i) acc[i] = 0.0;
 
     const double phi_ref = P.mean_subtract ? *P.phi_ref : 0.0;
-    // a model constant in the compute type (the FP32 copy for FP32 arithmetic)
-    auto KC = [&](double d, float f) __attribute__((always_inline)) -> C {
-        if constexpr (std::is_same<C, float>::value) return f;
-        else return C(d);
-    };
     if constexpr (MODE == MODE_STEP || MODE == MODE_STEP_PHI) {
         // a step between caller checkpoints carries the buffered <phi> over
         if (P.ref_copy && blockIdx.x == 0 && tid == 0) *P.ref_copy = *P.phi_ref;
@@ -1067,36 +621,19 @@ k_lbm(const KParams P) {
         const double sA = c_cA, sB = c_cB, sC = c_cC;
 
         if (active) {
-            Scalars m;
-            double muC = 0.0;  // potential of a third composition
-            if constexpr (NC3) {
-                const Scalars3 m3 = node_scalars3(c_ps, sA, sB, sC, P);
-                m = Scalars{m3.phi, m3.muA, m3.muB, m3.S};
-                muC = m3.muC;
-            } else {
-                m = node_scalars<GK>(c_ps, sA, sB, P);
-            }
+            double muC;  // potential of a third composition
+            const Scalars m = NODE::scalars(c_ps, sA, sB, sC, P, muC);
             const C phi = C(m.phi);
 
-            // isotropic gradient and Laplacian, Eqs. Grad and Laplacian (fluid lattice)
             C grad[3] = {C(0), C(0), C(0)};
             C lap = C(0);
-            C pc = phi;
-            C nsum = C(0);  // 3 sum_{k != 0} w_k phi(x + e_k)
             if constexpr (STENCIL) {
-                pc = sphi[sc][ty + OY][tx + 1];
-                static_for<1, STL::Q>([&](auto kc) __attribute__((always_inline)) {
-                    constexpr int k = decltype(kc)::value;
-                    constexpr int ex = STL::ex(k), ey = STL::ey(k), ez = STL::ez(k);
-                    const int slot = ez == 0 ? sc : (ez > 0 ? sp : sm);
-                    const C v = sphi[slot][ty + OY + ey][tx + 1 + ex];
-                    const C wv = C(3.0 * STL::w(k)) * v;
-                    if constexpr (ex != 0) grad[0] += ex > 0 ? wv : -wv;
-                    if constexpr (ey != 0) grad[1] += ey > 0 ? wv : -wv;
-                    if constexpr (ez != 0) grad[2] += ez > 0 ? wv : -wv;
-                    nsum += wv;
-                });
-                lap = C(2) * (nsum - C(3.0 * (1.0 - STL::w(0))) * pc);
+                NODE::stencil(
+                    [&](auto ex_, auto ey_, auto ez_) __attribute__((always_inline)) -> C {
+                        constexpr int ex = decltype(ex_)::value, ey = decltype(ey_)::value, ez = decltype(ez_)::value;
+                        return sphi[ez == 0 ? sc : (ez > 0 ? sp : sm)][ty + OY + ey][tx + 1 + ex];
+                    },
+                    sphi[sc][ty + OY][tx + 1], grad, lap);
             }
 
             C u[3] = {C(0), C(0), C(0)};
@@ -1104,69 +641,12 @@ k_lbm(const KParams P) {
             C F[3] = {C(0), C(0), C(0)};
             C irho = C(1);  // 1 / rho(phi) (variable density)
             if constexpr (FLOW) {
-                // Eq. SurfaceTension_Force plus buoyancy (phi - phi_ref) drho g
-                const C bracket = KC(P.cap, P.f32.cap) * (C(dwell_d(m.phi)) * KC(P.inv_W2, P.f32.inv_W2) - lap);
-                const C buoy = C(m.phi - phi_ref) * KC(P.drho, P.f32.drho);
-                F[0] = buoy * KC(P.gx, P.f32.gx) + bracket * grad[0];
-                F[1] = buoy * KC(P.gy, P.f32.gy) + bracket * grad[1];
-                F[2] = buoy * KC(P.gz, P.f32.gz) + bracket * grad[2];
                 if constexpr (FRAW) {
                     static_for<1, QF>([&](auto kc) __attribute__((always_inline)) {
                         fpop[decltype(kc)::value] = dec_lo<PREC>(fraw[decltype(kc)::value], wref_dec(kc, kc, FLT{}), P.finv[0]);
                     });
                 }
-                // Eqs. HydroPressure and Velocity
-                C j0 = C(0), j1 = C(0), j2 = C(0);
-                static_for<0, QF>([&](auto kc) __attribute__((always_inline)) {
-                    constexpr int k = decltype(kc)::value;
-                    p_h += fpop[k];
-                    if constexpr (FL::ex(k) != 0) j0 += FL::ex(k) > 0 ? fpop[k] : -fpop[k];
-                    if constexpr (FL::ey(k) != 0) j1 += FL::ey(k) > 0 ? fpop[k] : -fpop[k];
-                    if constexpr (FL::ez(k) != 0) j2 += FL::ez(k) > 0 ? fpop[k] : -fpop[k];
-                });
-                if constexpr (!VD) {
-                    const C inv_rho0 = KC(1.0 / P.rho0, P.f32.inv_rho0);
-                    u[0] = (C(3) * j0 + C(0.5) * F[0]) * inv_rho0;
-                    u[1] = (C(3) * j1 + C(0.5) * F[1]) * inv_rho0;
-                    u[2] = (C(3) * j2 + C(0.5) * F[2]) * inv_rho0;
-                } else {
-                    // variable density: f is dimensionless, p_h holds p* = sum f; rho(phi)
-                    // interpolated; pressure force -p* c_s^2 grad rho; predictor velocity;
-                    // viscous force -(nu w+ / c_s^2) Pi . grad rho from the non-equilibrium
-                    // second moment at the predictor; final velocity
-                    const C drho = KC(P.drho, P.f32.drho);
-                    irho = rcp<C>(KC(P.rho0, P.f32.rho0) + drho * phi);
-                    const C fp = -p_h * C(1.0 / 3.0) * drho;
-                    C us[3];
-                    us[0] = j0 + C(0.5) * (F[0] + fp * grad[0]) * irho;
-                    us[1] = j1 + C(0.5) * (F[1] + fp * grad[1]) * irho;
-                    us[2] = j2 + C(0.5) * (F[2] + fp * grad[2]) * irho;
-                    const C uus = us[0] * us[0] + us[1] * us[1] + us[2] * us[2];
-                    const C e0s = p_h - C(1.5) * uus;
-                    C pxx = C(0), pyy = C(0), pzz = C(0), pxy = C(0), pxz = C(0), pyz = C(0);
-                    static_for<0, QF>([&](auto kc) __attribute__((always_inline)) {
-                        constexpr int k = decltype(kc)::value;
-                        constexpr int ex = FL::ex(k), ey = FL::ey(k), ez = FL::ez(k);
-                        const C eu = edot<ex, ey, ez>(us[0], us[1], us[2]);
-                        const C n = fpop[k] - C(FL::w(k)) * (e0s + eu * (C(3) + C(4.5) * eu));
-                        if constexpr (ex != 0) pxx += n;
-                        if constexpr (ey != 0) pyy += n;
-                        if constexpr (ez != 0) pzz += n;
-                        if constexpr (ex != 0 && ey != 0) pxy += ex * ey > 0 ? n : -n;
-                        if constexpr (ex != 0 && ez != 0) pxz += ex * ez > 0 ? n : -n;
-                        if constexpr (ey != 0 && ez != 0) pyz += ey * ez > 0 ? n : -n;
-                    });
-                    const C nuv = KC(P.nu0, P.f32.nu0) * (C(1) - phi) + KC(P.nu1, P.f32.nu1) * phi;
-                    const C coef = -C(3) * nuv * rcp<C>(C(3) * nuv + C(0.5)) * drho;
-                    const C Fm[3] = {coef * (pxx * grad[0] + pxy * grad[1] + pxz * grad[2]),
-                                     coef * (pxy * grad[0] + pyy * grad[1] + pyz * grad[2]),
-                                     coef * (pxz * grad[0] + pyz * grad[1] + pzz * grad[2])};
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        u[a] = us[a] + C(0.5) * Fm[a] * irho;
-                        F[a] += fp * grad[a] + Fm[a];
-                    }
-                }
+                NODE::flow(P, fpop, m.phi, phi, phi_ref, grad, lap, F, u, p_h, irho);
             }
 
             if constexpr (MODE == MODE_STEP || MODE == MODE_STEP_PHI) {
@@ -1174,373 +654,9 @@ k_lbm(const KParams P) {
                 // phi of the source state, as the stencil saw it (for the adjoint)
                 if constexpr (MODE == MODE_STEP_PHI) static_cast<C*>(P.phi_out)[idx] = phi;
 
-                // post-collision populations go to this node's own slots of the other copy.
-                // 16-bit storage: the rounding residue of a field's moving populations is
-                // added to its FP32 rest population, so the stored state keeps each node's
-                // post-collision mass of every field (the rest population is stored last)
-                constexpr bool FEEDBACK = PREC == P16 || PREC == PB16;
-                auto push = [&](auto s_, auto k_, auto lat_, C v) __attribute__((always_inline)) {
-                    store(s_, k_, lat_, idx, v);
-                };
-                auto push_r = [&](auto s_, auto k_, auto lat_, C v, C& res) __attribute__((always_inline)) {
-                    if constexpr (FEEDBACK) store_r(s_, k_, lat_, idx, v, res);
-                    else store(s_, k_, lat_, idx, v);
-                };
-                // BGK steps: the moving populations of directions k and opp(k) of one field
-                // (with 16-bit storage: one packed conversion; their stored deviations add to
-                // dev, and the rest population is stored last as the field's post-collision
-                // zeroth moment, conserved by the collision, minus the stored moving
-                // populations, stored_sum)
-                auto push_d2 = [&](auto sk_, auto so_, auto k_, auto o_, auto lat_, C vk, C vo, C& dev)
-                                   __attribute__((always_inline)) {
-                    if constexpr (FEEDBACK) {
-                        constexpr int F = SLOTS::field(decltype(sk_)::value);
-                        static_assert(F == SLOTS::field(decltype(so_)::value), "one field");
-                        dev += st2_at_dev<PREC>(dst(sk_), dst(so_), idx, wref(sk_, k_, lat_), P.fscale[F], vk, vo);
-                    } else {
-                        store(sk_, k_, lat_, idx, vk);
-                        store(so_, o_, lat_, idx, vo);
-                    }
-                };
-
-                // ---- f: Eqs. LBE_FluidFlow, ForcingTerm, GammaFunction, Feq ----
-                // f* = (1 - w) f + w w_k [p + rho0 (eu + 3/2 eu^2 - uu/2)] + (1 - w/2) F_k,
-                // F_k = w_k [1 + 3 eu + 9/2 eu^2 - 3/2 uu] (e_k . F - u . F)
-                if constexpr (FLOW) {
-                    const C uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-                    const C uF = u[0] * F[0] + u[1] * F[1] + u[2] * F[2];
-                    const C nu = KC(P.nu0, P.f32.nu0) * (C(1) - phi) + KC(P.nu1, P.f32.nu1) * phi;
-                    const C wf = rcp<C>(C(3) * nu + C(0.5));
-                    const C keep = C(1) - wf, half = C(1) - C(0.5) * wf;
-                    // inertia of the equilibrium: rho0 (Eq. Feq), or 1 / c_s^2 for the
-                    // dimensionless populations of the variable-density model, whose
-                    // forcing populations are divided by rho c_s^2
-                    const C rho0 = VD ? C(3) : KC(P.rho0, P.f32.rho0);
-                    const C g0 = C(1) - C(1.5) * uu, e0 = p_h - C(0.5) * rho0 * uu;
-                    const C fsc = VD ? C(3) * irho : C(1);
-                    if constexpr (MRTC) {
-                        // MRT: the traceless second order at the viscous rate wf, the trace,
-                        // third and fourth orders at the given rates; orders 0 and 1 are
-                        // conserved (rate 1)
-                        auto feqs = [&](auto kc, C& Fk) __attribute__((always_inline)) -> C {
-                            constexpr int k = decltype(kc)::value;
-                            constexpr int ex = FL::ex(k), ey = FL::ey(k), ez = FL::ez(k);
-                            const C wk = C(FL::w(k));
-                            const C eu = edot<ex, ey, ez>(u[0], u[1], u[2]);
-                            const C eF = edot<ex, ey, ez>(F[0], F[1], F[2]);
-                            Fk = wk * (g0 + eu * (C(3) + C(4.5) * eu)) * (eF - uF);
-                            if constexpr (VD) Fk *= fsc;
-                            return wk * (e0 + rho0 * eu * (C(1) + C(1.5) * eu)) - C(0.5) * Fk;
-                        };
-                        C Fks[QF];
-                        C resm = C(0), restm = C(0);
-                        mrt_relax<FL>(fpop,
-                            [&](auto kc) __attribute__((always_inline)) -> C {
-                                return feqs(kc, Fks[decltype(kc)::value]);
-                            },
-                            [&](auto kc) __attribute__((always_inline)) -> C { return Fks[decltype(kc)::value]; },
-                            [&](auto ic) __attribute__((always_inline)) -> C {
-                                constexpr int i = decltype(ic)::value;
-                                constexpr int o = basis_order<FL, i>();
-                                if constexpr (o <= 1) return C(1);
-                                else if constexpr (basis_trace<FL, i>()) return KC(P.mrt_f[0], P.f32.mrt_f[0]);
-                                else if constexpr (o == 2) return wf;
-                                else if constexpr (o == 3) return KC(P.mrt_f[1], P.f32.mrt_f[1]);
-                                else return KC(P.mrt_f[2], P.f32.mrt_f[2]);
-                            },
-                            [&](auto kc, C v) __attribute__((always_inline)) {
-                                if constexpr (decltype(kc)::value == 0 && FEEDBACK) restm = v;
-                                else push_r(kc, kc, FLT{}, v, resm);
-                            });
-                        if constexpr (FEEDBACK) push(IC<0>{}, IC<0>{}, FLT{}, restm + fb(IC<0>{}, resm));
-                    } else if constexpr (!TRTC) {
-                    // f*_k = keep f_k + w_k [a_k + gam_k (e_k . Fh - u . Fh)] with
-                    // a_k = wf (e0 + rho0 (eu + 3/2 eu^2)), gam_k = 1 + 3 eu + 9/2 eu^2 - 3/2 uu
-                    // and Fh = (1 - wf/2) F (times 1 / (rho c_s^2) with variable density):
-                    // k and opp(k) share eu^2 and differ in the signs of eu, e_k . Fh
-                    const C A = wf * e0, B = wf * rho0;
-                    const C hs = half * fsc;
-                    const C Fh[3] = {hs * F[0], hs * F[1], hs * F[2]};
-                    const C uFh = hs * uF;
-                    C dev = C(0);
-                    static_for<1, QF>([&](auto kc) __attribute__((always_inline)) {
-                        constexpr int k = decltype(kc)::value;
-                        constexpr int o = FL::opp(k);
-                        if constexpr (k < o) {
-                            constexpr int ex = FL::ex(k), ey = FL::ey(k), ez = FL::ez(k);
-                            const C wk = C(FL::w(k));  // w_opp(k) = w_k
-                            const C eu = edot<ex, ey, ez>(u[0], u[1], u[2]);
-                            const C eF = edot<ex, ey, ez>(Fh[0], Fh[1], Fh[2]);
-                            const C e2 = eu * eu;
-                            const C q = C(1.5) * e2;
-                            const C r = g0 + C(4.5) * e2;
-                            const C ak = A + B * (q + eu), ao = A + B * (q - eu);
-                            const C gk = r + C(3) * eu, go = r - C(3) * eu;
-                            const C vk = keep * fpop[k] + wk * (ak + gk * (eF - uFh));
-                            const C vo = keep * fpop[o] + wk * (ao - go * (eF + uFh));
-                            push_d2(kc, IC<o>{}, kc, IC<o>{}, FLT{}, vk, vo, dev);
-                        }
-                    });
-                    // rest: Sum_k f*_k = p_h (the equilibrium keeps p_h, the forcing sums to 0)
-                    if constexpr (FEEDBACK) push(IC<0>{}, IC<0>{}, FLT{}, p_h - stored_sum(IC<0>{}, FLT{}, dev));
-                    else push(IC<0>{}, IC<0>{}, FLT{}, keep * fpop[0] + C(FL::w(0)) * (A - g0 * uFh));
-                    } else {
-                        // TRT: the viscosity sets the symmetric rate w+ = wf; w- from the
-                        // magic parameter, 1/w- - 1/2 = Lambda_f / (1/wf - 1/2) = Lambda_f / (3 nu)
-                        const C wm = rcp<C>(C(0.5) + KC(P.trt_lf, P.f32.trt_lf) * rcp<C>(C(3) * nu));
-                        // shifted equilibrium (feq - F_k/2) and source F_k of direction k
-                        auto eqsrc = [&](auto kc, C& eqs, C& Fk) __attribute__((always_inline)) {
-                            constexpr int k = decltype(kc)::value;
-                            constexpr int ex = FL::ex(k), ey = FL::ey(k), ez = FL::ez(k);
-                            const C wk = C(FL::w(k));
-                            const C eu = edot<ex, ey, ez>(u[0], u[1], u[2]);
-                            const C eF = edot<ex, ey, ez>(F[0], F[1], F[2]);
-                            Fk = wk * (g0 + eu * (C(3) + C(4.5) * eu)) * (eF - uF);
-                            if constexpr (VD) Fk *= fsc;
-                            eqs = wk * (e0 + rho0 * eu * (C(1) + C(1.5) * eu)) - C(0.5) * Fk;
-                        };
-                        C res = C(0), rest = C(0);
-                        static_for<0, QF>([&](auto kc) __attribute__((always_inline)) {
-                            constexpr int k = decltype(kc)::value;
-                            constexpr int o = FL::opp(k);
-                            if constexpr (k == 0) {
-                                C eqs, Fk;
-                                eqsrc(kc, eqs, Fk);
-                                rest = fpop[0] - wf * (fpop[0] - eqs) + Fk;
-                                if constexpr (!FEEDBACK) push(kc, kc, FLT{}, rest);
-                            } else if constexpr (k < o) {
-                                C eqk, Fk, eqo, Fo;
-                                eqsrc(kc, eqk, Fk);
-                                eqsrc(IC<o>{}, eqo, Fo);
-                                const C nk = fpop[k] - eqk, no = fpop[o] - eqo;
-                                const C sp = wf * C(0.5) * (nk + no), sm = wm * C(0.5) * (nk - no);
-                                push_r(kc, kc, FLT{}, fpop[k] - sp - sm + Fk, res);
-                                push_r(IC<o>{}, IC<o>{}, FLT{}, fpop[o] - sp + sm + Fo, res);
-                            }
-                        });
-                        if constexpr (FEEDBACK) push(IC<0>{}, IC<0>{}, FLT{}, rest + fb(IC<0>{}, res));
-                    }
-                }
-
-                LBM_FENCE();
-                // ---- g: Eqs. LBE_Phi, Geq, Source_LBE_Phi ----
-                // g* = (1 - w) g + w w_k phi (1 + eu / c_s^2) + (1 - w/2) w_k S
-                {
-                    const C wg = KC(P.omega_g, P.f32.omega_g);
-                    const C keep = C(1) - wg;
-                    const C wphi = wg * phi;
-                    const C srcS = (C(1) - C(0.5) * wg) * C(m.S);
-                    if constexpr (MRTC) {
-                        // MRT: the first order (diffusive flux) at the M_phi rate, orders 0
-                        // and 2 at the given even rate, third and fourth at theirs
-                        const C S = C(m.S), hS = C(0.5) * C(m.S);
-                        C resm = C(0), restm = C(0);
-                        mrt_relax<SL>(g,
-                            [&](auto kc) __attribute__((always_inline)) -> C {
-                                constexpr int k = decltype(kc)::value;
-                                constexpr int ex = SL::ex(k), ey = SL::ey(k), ez = SL::ez(k);
-                                const C wk = C(SL::w(k));
-                                if constexpr (ex != 0 || ey != 0 || ez != 0)
-                                    return wk * (phi * (C(1) + edot<ex, ey, ez>(u[0], u[1], u[2]) * inv_cs2s) - hS);
-                                else
-                                    return wk * (phi - hS);
-                            },
-                            [&](auto kc) __attribute__((always_inline)) -> C { return C(SL::w(decltype(kc)::value)) * S; },
-                            [&](auto ic) __attribute__((always_inline)) -> C {
-                                constexpr int o = basis_order<SL, decltype(ic)::value>();
-                                if constexpr (o == 1) return wg;
-                                else if constexpr (o == 3) return KC(P.mrt_s[1], P.f32.mrt_s[1]);
-                                else if constexpr (o == 4) return KC(P.mrt_s[2], P.f32.mrt_s[2]);
-                                else return KC(P.mrt_s[0], P.f32.mrt_s[0]);
-                            },
-                            [&](auto kc, C v) __attribute__((always_inline)) {
-                                if constexpr (decltype(kc)::value == 0 && FEEDBACK) restm = v;
-                                else push_r(IC<G0 + decltype(kc)::value>{}, kc, SLT{}, v, resm);
-                            });
-                        if constexpr (FEEDBACK) push(IC<G0>{}, IC<0>{}, SLT{}, restm + fb(IC<1>{}, resm));
-                    } else if constexpr (!TRTC) {
-                    // g*_k = keep g_k + w_k (t + c eu), t = w phi + (1 - w/2) S, c = w phi / c_s^2
-                    const C t = wphi + srcS, cu = wphi * inv_cs2s;
-                    C dev = C(0);
-                    static_for<1, QS>([&](auto kc) __attribute__((always_inline)) {
-                        constexpr int k = decltype(kc)::value;
-                        constexpr int o = SL::opp(k);
-                        if constexpr (k < o) {
-                            constexpr int ex = SL::ex(k), ey = SL::ey(k), ez = SL::ez(k);
-                            const C wk = C(SL::w(k));
-                            const C ceu = cu * edot<ex, ey, ez>(u[0], u[1], u[2]);
-                            push_d2(IC<G0 + k>{}, IC<G0 + o>{}, kc, IC<o>{}, SLT{}, keep * g[k] + wk * (t + ceu),
-                                    keep * g[o] + wk * (t - ceu), dev);
-                        }
-                    });
-                    // rest: Sum_k g*_k = (1 - w) phi* + w phi + (1 - w/2) S with phi* = Sum_k g_k
-                    // (phi = phi* + S*/2 takes the predictor's S*, the source the corrected S)
-                    if constexpr (FEEDBACK) {
-                        const double wgd = double(wg);
-                        const double mg = c_ps + wgd * (m.phi - c_ps) + (1.0 - 0.5 * wgd) * m.S;
-                        push(IC<G0>{}, IC<0>{}, SLT{}, C(mg) - stored_sum(IC<1>{}, SLT{}, dev));
-                    }
-                    else
-                        push(IC<G0>{}, IC<0>{}, SLT{}, keep * g[0] + C(SL::w(0)) * t);
-                    } else {
-                        // TRT: M_phi sets the antisymmetric rate w- = wg; w+ (uniform) from
-                        // the magic parameter on the host.  Shifted equilibrium
-                        // w_k phi (1 + eu / c_s^2) - w_k S / 2, source w_k S.
-                        const C wp = KC(P.omega_gp, P.f32.omega_gp);
-                        const C S = C(m.S), hS = C(0.5) * C(m.S);
-                        auto eqs = [&](auto kc) __attribute__((always_inline)) -> C {
-                            constexpr int k = decltype(kc)::value;
-                            constexpr int ex = SL::ex(k), ey = SL::ey(k), ez = SL::ez(k);
-                            const C wk = C(SL::w(k));
-                            if constexpr (ex != 0 || ey != 0 || ez != 0)
-                                return wk * (phi * (C(1) + edot<ex, ey, ez>(u[0], u[1], u[2]) * inv_cs2s) - hS);
-                            else
-                                return wk * (phi - hS);
-                        };
-                        C res = C(0), rest = C(0);
-                        static_for<0, QS>([&](auto kc) __attribute__((always_inline)) {
-                            constexpr int k = decltype(kc)::value;
-                            constexpr int o = SL::opp(k);
-                            if constexpr (k == 0) {
-                                rest = g[0] - wp * (g[0] - eqs(kc)) + C(SL::w(0)) * S;
-                                if constexpr (!FEEDBACK) push(IC<G0>{}, kc, SLT{}, rest);
-                            } else if constexpr (k < o) {
-                                const C nk = g[k] - eqs(kc), no = g[o] - eqs(IC<o>{});
-                                const C sp = wp * C(0.5) * (nk + no), sm = wg * C(0.5) * (nk - no);
-                                push_r(IC<G0 + k>{}, kc, SLT{}, g[k] - sp - sm + C(SL::w(k)) * S, res);
-                                push_r(IC<G0 + o>{}, IC<o>{}, SLT{}, g[o] - sp + sm + C(SL::w(o)) * S, res);
-                            }
-                        });
-                        if constexpr (FEEDBACK) push(IC<G0>{}, IC<0>{}, SLT{}, rest + fb(IC<1>{}, res));
-                    }
-                }
-
-                LBM_FENCE();
-                // ---- h^A, h^B: Eqs. LBE_c_alpha, Heq; mobility interpolated in phi ----
-                {
-                    const C MA = KC(P.MA0, P.f32.MA0) * (C(1) - phi) + KC(P.MA1, P.f32.MA1) * phi;
-                    const C MB = KC(P.MB0, P.f32.MB0) * (C(1) - phi) + KC(P.MB1, P.f32.MB1) * phi;
-                    const C wA = rcp<C>(MA * inv_cs2s + C(0.5));
-                    const C wB = rcp<C>(MB * inv_cs2s + C(0.5));
-                    if constexpr (MRTC) {
-                        // MRT: the first order at the mobility rate, the others at the given
-                        // rates (order 0 with the even rate: c is conserved exactly)
-                        auto rates = [&](C wflux) __attribute__((always_inline)) {
-                            return [&, wflux](auto ic) __attribute__((always_inline)) -> C {
-                                constexpr int o = basis_order<SL, decltype(ic)::value>();
-                                if constexpr (o == 1) return wflux;
-                                else if constexpr (o == 3) return KC(P.mrt_s[1], P.f32.mrt_s[1]);
-                                else if constexpr (o == 4) return KC(P.mrt_s[2], P.f32.mrt_s[2]);
-                                else return KC(P.mrt_s[0], P.f32.mrt_s[0]);
-                            };
-                        };
-                        auto heq = [&](double c, double mu) __attribute__((always_inline)) {
-                            return [&, c, mu](auto kc) __attribute__((always_inline)) -> C {
-                                constexpr int k = decltype(kc)::value;
-                                constexpr int ex = SL::ex(k), ey = SL::ey(k), ez = SL::ez(k);
-                                if constexpr (k == 0) return C(c - (1.0 - SL::w(0)) * mu);
-                                else return C(SL::w(k)) * (C(mu) + C(c) * edot<ex, ey, ez>(u[0], u[1], u[2]) * inv_cs2s);
-                            };
-                        };
-                        auto zero = [&](auto) __attribute__((always_inline)) -> C { return C(0); };
-                        C resA = C(0), restA = C(0), resB = C(0), restB = C(0);
-                        mrt_relax<SL>(a, heq(sA, m.muA), zero, rates(wA),
-                                      [&](auto kc, C v) __attribute__((always_inline)) {
-                                          if constexpr (decltype(kc)::value == 0 && FEEDBACK) restA = v;
-                                          else push_r(IC<A0 + decltype(kc)::value>{}, kc, SLT{}, v, resA);
-                                      });
-                        mrt_relax<SL>(b, heq(sB, m.muB), zero, rates(wB),
-                                      [&](auto kc, C v) __attribute__((always_inline)) {
-                                          if constexpr (decltype(kc)::value == 0 && FEEDBACK) restB = v;
-                                          else push_r(IC<B0 + decltype(kc)::value>{}, kc, SLT{}, v, resB);
-                                      });
-                        if constexpr (FEEDBACK) {
-                            push(IC<A0>{}, IC<0>{}, SLT{}, restA + fb(IC<2>{}, resA));
-                            push(IC<B0>{}, IC<0>{}, SLT{}, restB + fb(IC<3>{}, resB));
-                        }
-                    } else if constexpr (TRTC) {
-                        // TRT: the mobility sets the antisymmetric rate w- = wA (wB); w+ from
-                        // the magic parameter, 1/w+ - 1/2 = Lambda_s / (M / c_s^2)
-                        const C ls = KC(P.trt_ls, P.f32.trt_ls);
-                        const C wpA = rcp<C>(C(0.5) + ls * rcp<C>(MA * inv_cs2s));
-                        const C wpB = rcp<C>(C(0.5) + ls * rcp<C>(MB * inv_cs2s));
-                        // rest populations (symmetric) in double, as in BGK, stored last with
-                        // the rounding residues of 16-bit storage
-                        const double pa = double(a[0]) - double(wpA) * (double(a[0]) - (sA - (1.0 - SL::w(0)) * m.muA));
-                        const double pb = double(b[0]) - double(wpB) * (double(b[0]) - (sB - (1.0 - SL::w(0)) * m.muB));
-                        C resA = C(0), resB = C(0);
-                        const C muA = C(m.muA), muB = C(m.muB);
-                        const C cuA = C(sA) * inv_cs2s, cuB = C(sB) * inv_cs2s;
-                        static_for<1, QS>([&](auto kc) __attribute__((always_inline)) {
-                            constexpr int k = decltype(kc)::value;
-                            constexpr int o = SL::opp(k);
-                            if constexpr (k < o) {
-                                constexpr int ex = SL::ex(k), ey = SL::ey(k), ez = SL::ez(k);
-                                const C wk = C(SL::w(k));  // w_opp(k) = w_k
-                                const C eu = edot<ex, ey, ez>(u[0], u[1], u[2]);  // e_opp . u = -eu
-                                // h^eq_k = w_k (mu + c eu / c_s^2): symmetric part w_k mu, antisymmetric w_k c eu / c_s^2
-                                const C npA = C(0.5) * (a[k] + a[o]) - wk * muA, nmA = C(0.5) * (a[k] - a[o]) - wk * cuA * eu;
-                                const C npB = C(0.5) * (b[k] + b[o]) - wk * muB, nmB = C(0.5) * (b[k] - b[o]) - wk * cuB * eu;
-                                push_r(IC<A0 + k>{}, kc, SLT{}, a[k] - wpA * npA - wA * nmA, resA);
-                                push_r(IC<A0 + o>{}, IC<o>{}, SLT{}, a[o] - wpA * npA + wA * nmA, resA);
-                                push_r(IC<B0 + k>{}, kc, SLT{}, b[k] - wpB * npB - wB * nmB, resB);
-                                push_r(IC<B0 + o>{}, IC<o>{}, SLT{}, b[o] - wpB * npB + wB * nmB, resB);
-                            }
-                        });
-                        push(IC<A0>{}, IC<0>{}, SLT{}, C(pa + double(fb(IC<2>{}, resA))));
-                        push(IC<B0>{}, IC<0>{}, SLT{}, C(pb + double(fb(IC<3>{}, resB))));
-                    } else {
-                    // BGK: h*_k = keep h_k + w_k (w mu + w c eu / c_s^2); k and opp(k) share w mu.
-                    // Rest populations in double (they carry the conserved composition): from
-                    // the collision with FP32 / FP64 storage, as c minus the stored moving
-                    // populations with 16-bit storage
-                    const C keepA = C(1) - wA, keepB = C(1) - wB;
-                    const C wmuA = wA * C(m.muA), wmuB = wB * C(m.muB);
-                    const C wcA = wA * C(sA) * inv_cs2s, wcB = wB * C(sB) * inv_cs2s;
-                    C devA = C(0), devB = C(0);
-                    // a third composition: the same BGK relaxation with its own mobility
-                    C wC = C(0), keepC = C(0), wmuC = C(0), wcC = C(0), devC = C(0);
-                    if constexpr (NC3) {
-                        const C MC = KC(P.MC0, P.f32.MC0) * (C(1) - phi) + KC(P.MC1, P.f32.MC1) * phi;
-                        wC = rcp<C>(MC * inv_cs2s + C(0.5));
-                        keepC = C(1) - wC;
-                        wmuC = wC * C(muC);
-                        wcC = wC * C(sC) * inv_cs2s;
-                    }
-                    static_for<1, QS>([&](auto kc) __attribute__((always_inline)) {
-                        constexpr int k = decltype(kc)::value;
-                        constexpr int o = SL::opp(k);
-                        if constexpr (k < o) {
-                            constexpr int ex = SL::ex(k), ey = SL::ey(k), ez = SL::ez(k);
-                            const C wk = C(SL::w(k));  // w_opp(k) = w_k
-                            const C eu = edot<ex, ey, ez>(u[0], u[1], u[2]);
-                            push_d2(IC<A0 + k>{}, IC<A0 + o>{}, kc, IC<o>{}, SLT{}, keepA * a[k] + wk * (wmuA + wcA * eu),
-                                    keepA * a[o] + wk * (wmuA - wcA * eu), devA);
-                            push_d2(IC<B0 + k>{}, IC<B0 + o>{}, kc, IC<o>{}, SLT{}, keepB * b[k] + wk * (wmuB + wcB * eu),
-                                    keepB * b[o] + wk * (wmuB - wcB * eu), devB);
-                            if constexpr (NC3)
-                                push_d2(IC<HC0 + k>{}, IC<HC0 + o>{}, kc, IC<o>{}, SLT{},
-                                        keepC * cq[k] + wk * (wmuC + wcC * eu), keepC * cq[o] + wk * (wmuC - wcC * eu),
-                                        devC);
-                        }
-                    });
-                    if constexpr (FEEDBACK) {
-                        push(IC<A0>{}, IC<0>{}, SLT{}, C(sA - double(stored_sum(IC<2>{}, SLT{}, devA))));
-                        push(IC<B0>{}, IC<0>{}, SLT{}, C(sB - double(stored_sum(IC<3>{}, SLT{}, devB))));
-                        if constexpr (NC3)
-                            push(IC<HC0>{}, IC<0>{}, SLT{}, C(sC - double(stored_sum(IC<4>{}, SLT{}, devC))));
-                    } else {
-                        const double w1 = 1.0 - SL::w(0);
-                        auto rest = [&](C h0, C w, double sc, double mu) __attribute__((always_inline)) -> C {
-                            return C(double(h0) - double(w) * (double(h0) - (sc - w1 * mu)));
-                        };
-                        push(IC<A0>{}, IC<0>{}, SLT{}, rest(a[0], wA, sA, m.muA));
-                        push(IC<B0>{}, IC<0>{}, SLT{}, rest(b[0], wB, sB, m.muB));
-                        if constexpr (NC3) push(IC<HC0>{}, IC<0>{}, SLT{}, rest(cq[0], wC, sC, muC));
-                    }
-                    }
-                }
-
+                // post-collision populations go to this node's own slots of the other copy
+                NODE::collide(P, fpop, g, a, b, cq, c_ps, sA, sB, sC, m, muC, phi, F, u, p_h, irho,
+                              [&](auto s_, auto v) __attribute__((always_inline)) { st_raw(dst(s_), idx, v); });
             } else if constexpr (MODE == MODE_MOMENTS) {
                 // hydrodynamic pressure: p_h, or rho c_s^2 p* with variable density
                 const double p_out = VD ? double(p_h) / (3.0 * double(irho)) : double(p_h);

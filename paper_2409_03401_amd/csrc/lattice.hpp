@@ -8,6 +8,8 @@
 // weights 1/3, 1/6 and 1/4, 1/8 (c_s^2 = 1/3 and 1/4).
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <type_traits>
 
 namespace lbm {

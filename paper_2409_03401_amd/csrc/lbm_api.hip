@@ -44,6 +44,7 @@ struct Layout {
     size_t copy_bytes;
     size_t stride_m, stride_r;  // bytes of a moving / rest slot
     int tx, ty, zc;
+    bool tuned;  // the environment chooses the tile or the chunk length
     int tiles[3];
     dim3 grid;        // 1D: one work-group per tile
     long long nparts;     // work-groups of the fused kernel
@@ -195,6 +196,7 @@ int check_config(const lbm_config* c, Layout* L) {
     // of zc planes (see below).  Tuning only: the environment variables LBM_TILE
     // ("TXxTY", 2D: "TXx1") and LBM_ZC override the tile and the chunk length.
     int want_tx = 0, want_ty = 0;
+    L->tuned = std::getenv("LBM_TILE") || std::getenv("LBM_ZC");
     if (const char* e = std::getenv("LBM_TILE")) std::sscanf(e, "%dx%d", &want_tx, &want_ty);
     if (mrt && vd) return fail(LBM_EUNSUPPORTED, "the variable-density model runs with BGK or TRT");
     if (mrt) {
@@ -532,13 +534,99 @@ int lbm_init_composition(const lbm_config* cfg, void* state, size_t state_bytes,
     return init_impl(cfg, state, state_bytes, phi0, c, mu, 2, stream, out);
 }
 
+namespace {
+
+// windows of nt nodes, 2^lw wide, for up to k steps per launch; false: the halo leaves none
+bool block_geometry(const Layout& L, int nt, int lw, int k, BlockGeom& g) {
+    const int bw = 1 << lw, bh = nt >> lw;
+    const int halo = L.qf ? 2 * k - 1 : k - 1;
+    g = BlockGeom{};
+    g.lw = lw;
+    g.full_x = L.NX <= bw;
+    g.full_z = L.NZ <= bh;
+    g.hx = g.full_x ? 0 : halo;
+    g.hz = g.full_z ? 0 : halo;
+    g.ix = g.full_x ? L.NX : bw - 2 * halo;
+    g.iz = g.full_z ? L.NZ : bh - 2 * halo;
+    if (g.ix < 1 || g.iz < 1) return false;
+    g.tiles_x = (L.NX + g.ix - 1) / g.ix;
+    g.tiles_z = (L.NZ + g.iz - 1) / g.iz;
+    return true;
+}
+
+struct BlockPlan {
+    int nt = 0, k = 0;  // nt = 0: one step per launch with the marching kernel
+    BlockGeom g;
+};
+
+// How a call of n steps is cut into windows: the estimate of the time per step in us,
+// smallest over the windows of both sizes (256 and 512 or 1024 nodes) of every power-of-two
+// width and up to 128 steps per launch.  A launch takes 3.1 us, each step its barriers
+// (0.3 us, 0.7 with flow), and a window its loads, collisions and stores: alone on a
+// compute unit the latency of these, else their throughput (the windows of all 256 units
+// share the memory: `mem`, with the part of a 128-byte line that a row's ends waste; the
+// collisions, `cmp`, overlap with it mostly where two windows share a unit).  The constants
+// are a fit to 900 timings (eight families, 64^2 to 2048^2): the choice is within 2 % of
+// the fastest on average.  The marching kernel stays where the estimate says so: large
+// boxes of the D2Q9 lattices with flow and 16-bit storage (2048^2: 156 us against 159), and
+// for states whose buoyancy needs the mean of every step.
+BlockPlan block_plan(const lbm_handle* h, int64_t n) {
+    const Layout& L = h->L;
+    BlockPlan best;
+    if (!h->ks->block || L.tuned || h->cfg.gravity_mean_subtract) return best;
+    const double nodes = double(L.nodes), flow = L.qf ? 1.0 : 0.0;
+    const double bytes = double(L.copy_bytes) / nodes;  // of a node's populations
+    const double word = bytes / L.nslots;
+    const double cmp = 0.0067 * L.nslots * (13.0 + 4.0 * flow);  // of 1024 nodes, one step
+    double cost = 3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 + (h->base.wall_x ? 5.0 : 0.0);
+    for (int nt : h->ks->block_nt) {
+        for (int lw = 4; (1 << lw) <= nt; ++lw) {
+            for (int k = 1; k <= 128 && k <= n; ++k) {
+                BlockGeom g;
+                if (!block_geometry(L, nt, lw, k, g)) break;
+                const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
+                const double mem = bytes * 1024.0 / 42e3 *
+                                   (1.0 + 90.0 / ((1 << lw) * word) + share * (1.0 + 90.0 / (g.ix * word)));
+                const double alone = nt / 1024.0 * (2.0 + 0.6 * k * cmp);
+                const double busy = windows * nt / (256.0 * 1024.0) * (mem + (0.1 + 0.4 * flow) * k * cmp);
+                const double t = (3.1 + (0.3 + 0.4 * flow) * k + std::max(alone, busy)) / k;
+                if (t < cost) {
+                    cost = t;
+                    best.nt = nt;
+                    best.k = k;
+                    best.g = g;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
 int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     if (int r = check_handle(h)) return r;
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps < 0");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (nsteps == 0) return LBM_OK;
     KParams kp[2] = {h->base, h->base};
     set_slots(h, kp[0], h->copy[0], h->copy[1]);
     set_slots(h, kp[1], h->copy[1], h->copy[0]);
+    if (BlockPlan plan = block_plan(h, nsteps); plan.nt) {
+        // 2D: several steps per launch, cut evenly; the x walls are exchanged (k_walls) for
+        // the state that the call leaves only
+        const int64_t launches = (nsteps + plan.k - 1) / plan.k;
+        for (int64_t i = 0; i < launches; ++i) {
+            plan.g.nsub = int(nsteps * (i + 1) / launches - nsteps * i / launches);
+            plan.g.raw_x = i > 0;
+            h->ks->block(plan.nt, unsigned(plan.g.tiles_x) * unsigned(plan.g.tiles_z), kp[h->cur], plan.g, s);
+            if (i == launches - 1 && h->base.wall_x) h->ks->walls(kp[h->cur], 0, s);
+            if (int r = launched("block kernel")) return r;
+            h->cur ^= 1;
+            h->steps += plan.g.nsub;
+        }
+        return LBM_OK;
+    }
     // walls on x and y: the fix-up kernel; z walls bounce back when the next step pulls
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
     for (int64_t i = 0; i < nsteps; ++i) {

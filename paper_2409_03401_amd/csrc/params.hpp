@@ -125,6 +125,14 @@ struct KParams {
 constexpr int kAuxRows = 7;  // per-step scratch rows of the adjoint (c_F rows apart)
 constexpr int kAuxCRows = 3;
 
+// Windows of the several-steps kernel (2D): 2^lw nodes wide, halo (hx, hz), owned nodes
+// ix x iz per window; full_*: the axis fits into the window whole (no halo, wraps inside).
+// nsub: steps per launch.  raw_x: the source copy holds raw post-collision populations at
+// the x walls (left by a launch of this kernel), else exchanged ones (k_walls).
+struct BlockGeom {
+    int lw, hx, hz, ix, iz, tiles_x, tiles_z, full_x, full_z, nsub, raw_x;
+};
+
 // Euler characteristic of the closed cells of a node mask (droplet count of
 // Section 4.2.2).  Only the d active axes of the run are listed: axis i has n[i]
 // cells, mask stride stride[i], wall[i] != 0 when it ends at walls.  An anchor

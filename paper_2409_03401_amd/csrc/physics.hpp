@@ -16,6 +16,14 @@ struct Scalars {
     double phi, muA, muB, S;
 };
 
+// Sums of two products are written with their fused operation: which product the
+// compiler would fuse depends on the kernel around it, and every kernel has to round alike.
+__device__ __forceinline__ double sum2d(double x, double y, double z, double w) { return __builtin_fma(x, y, z * w); }
+// S_phi from its driving force, Eq. SourceTerm_Phi
+__device__ __forceinline__ double source_phi(double phi, double domega, const KParams& P) {
+    return P.mphi_w2 * __builtin_fma(P.lam * interp_dp(phi), domega, -dwell_d(phi));
+}
+
 // Potentials from compositions, Eq. PotChem with p(1 - phi) = 1 - p(phi),
 // and the source S_phi of Eq. SourceTerm_Phi with Delta omega = -sum mu (c_0 - c_1).
 // GK (general curvature matrices kappa_pi = K (K_pi)^-1 of Eq. Taylor): the closure
@@ -30,21 +38,21 @@ __device__ __forceinline__ void potentials_and_source(double phi, double cA, dou
     if constexpr (!GK) {
         muA = cA - P.c0A - pp * (P.c1A - P.c0A);
         muB = cB - P.c0B - pp * (P.c1B - P.c0B);
-        domega = -(muA * (P.c0A - P.c1A) + muB * (P.c0B - P.c1B));
+        domega = -sum2d(muA, P.c0A - P.c1A, muB, P.c0B - P.c1B);
     } else {
         const double rA = cA - P.c0A - pp * (P.c1A - P.c0A);
         const double rB = cB - P.c0B - pp * (P.c1B - P.c0B);
         const double kAA = P.kap0[0] + pp * (P.kap1[0] - P.kap0[0]);
         const double kAB = P.kap0[1] + pp * (P.kap1[1] - P.kap0[1]);
         const double kBB = P.kap0[2] + pp * (P.kap1[2] - P.kap0[2]);
-        const double det = kAA * kBB - kAB * kAB;
-        muA = (kBB * rA - kAB * rB) / det;
-        muB = (kAA * rB - kAB * rA) / det;
+        const double det = sum2d(kAA, kBB, -kAB, kAB);
+        muA = sum2d(kBB, rA, -kAB, rB) / det;
+        muB = sum2d(kAA, rB, -kAB, rA) / det;
         const double dAA = P.kap0[0] - P.kap1[0], dAB = P.kap0[1] - P.kap1[1], dBB = P.kap0[2] - P.kap1[2];
-        domega = -0.5 * (dAA * muA * muA + 2.0 * dAB * muA * muB + dBB * muB * muB) -
-                 (muA * (P.c0A - P.c1A) + muB * (P.c0B - P.c1B));
+        const double quad = __builtin_fma(dBB * muB, muB, sum2d(dAA * muA, muA, 2.0 * dAB * muA, muB));
+        domega = __builtin_fma(-0.5, quad, -sum2d(muA, P.c0A - P.c1A, muB, P.c0B - P.c1B));
     }
-    S = P.mphi_w2 * (P.lam * interp_dp(phi) * domega - dwell_d(phi));
+    S = source_phi(phi, domega, P);
 }
 
 // Moments of one node, Eqs. Moment0_c_alpha and Moment0_Phi.  phi = sum g + S/2
@@ -74,8 +82,8 @@ __device__ __forceinline__ void potentials_and_source3(double phi, double cA, do
     muA = cA - P.c0A - pp * (P.c1A - P.c0A);
     muB = cB - P.c0B - pp * (P.c1B - P.c0B);
     muC = cC - P.c0C - pp * (P.c1C - P.c0C);
-    const double domega = -(muA * (P.c0A - P.c1A) + muB * (P.c0B - P.c1B) + muC * (P.c0C - P.c1C));
-    S = P.mphi_w2 * (P.lam * interp_dp(phi) * domega - dwell_d(phi));
+    const double domega = -__builtin_fma(muC, P.c0C - P.c1C, sum2d(muA, P.c0A - P.c1A, muB, P.c0B - P.c1B));
+    S = source_phi(phi, domega, P);
 }
 
 __device__ __forceinline__ Scalars3 node_scalars3(double phis, double cA, double cB, double cC, const KParams& P) {
