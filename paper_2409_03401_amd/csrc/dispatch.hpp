@@ -6,7 +6,7 @@
 namespace lbm {
 
 struct KernelSet {
-    // fused kernel in MODE_STEP / MODE_MOMENTS / MODE_DIAG
+    // fused kernel in one of the modes (enum Mode)
     void (*fused)(int mode, dim3 grid, const KParams& kp, hipStream_t s);
     // equilibrium initialisation, one thread per node (muC0: the third composition's
     // potential, families with three compositions only)

@@ -21,6 +21,12 @@ struct Family {
                 if constexpr (NC == 2)
                     hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP_PHI, PREC, TX, TY, COLL>), grid, block, 0, s, kp);
                 break;
+            case MODE_SCALARS:
+                if constexpr (FL::Q > 0) {
+                    hipLaunchKernelGGL((k_lbm<SL, FL, MODE_SCALARS, PREC, TX, TY, (COLL & COLL_GK), NC>), grid, block, 0, s, kp);
+                    break;
+                }
+                [[fallthrough]];
             case MODE_MOMENTS:
                 hipLaunchKernelGGL((k_lbm<SL, FL, MODE_MOMENTS, PREC, TX, TY, (COLL & (COLL_VD | COLL_GK)), NC>), grid,
                                    block, 0, s, kp);

@@ -136,7 +136,7 @@ k_lbm(const KParams P) {
     using SLOTS = Slots<FL::Q, SL::Q, NC>;
     constexpr int QS = SL::Q;
     constexpr int QF = FL::Q;
-    constexpr bool FLOW = QF > 0;
+    constexpr bool FLOW = QF > 0 && MODE != MODE_SCALARS;
     constexpr bool STENCIL = FLOW || MODE == MODE_DIAG;
     constexpr bool HAS_Y = SL::DIM == 3;
     using NODE = Node<SL, FL, PREC, COLL, NC>;
@@ -657,9 +657,9 @@ k_lbm(const KParams P) {
                 // post-collision populations go to this node's own slots of the other copy
                 NODE::collide(P, fpop, g, a, b, cq, c_ps, sA, sB, sC, m, muC, phi, F, u, p_h, irho,
                               [&](auto s_, auto v) __attribute__((always_inline)) { st_raw(dst(s_), idx, v); });
-            } else if constexpr (MODE == MODE_MOMENTS) {
+            } else if constexpr (MODE == MODE_MOMENTS || MODE == MODE_SCALARS) {
                 // hydrodynamic pressure: p_h, or rho c_s^2 p* with variable density
-                const double p_out = VD ? double(p_h) / (3.0 * double(irho)) : double(p_h);
+                const double p_out = VD && FLOW ? double(p_h) / (3.0 * double(irho)) : double(p_h);
                 const double vals[kNumMom] = {m.phi, sA, sB, m.muA, m.muB, p_out,
                                               double(u[0]), double(u[1]), double(u[2]), sC, muC};
                 constexpr int NMOM = NC3 ? kNumMom : kNumMom - 2;

@@ -46,7 +46,7 @@ struct Layout {
     int tx, ty, zc;
     bool tuned;  // the environment chooses the tile or the chunk length
     int tiles[3];
-    dim3 grid;        // 1D: one work-group per tile
+    int zc_flat;      // chunk length of the kernels without the phi stencil
     long long nparts;     // work-groups of the fused kernel
     size_t aux_bytes;
     size_t mask_off;  // diagnostics mask (1 byte per node) after the aux area
@@ -251,7 +251,11 @@ int check_config(const lbm_config* c, Layout* L) {
     L->zc = zc;
     const long long gz = (L->NZ + zc - 1) / zc;
     L->tiles[0] = int(gx); L->tiles[1] = int(gy); L->tiles[2] = int(gz);
-    L->grid = dim3(unsigned(gx * gy * gz));
+    // Without the phi stencil (no flow, or moments of the scalars alone) a plane needs
+    // nothing of the one before: in 3D one plane per work-group, two on large grids, so that
+    // the loads of many groups overlap (96^3 FP64 step 67.2 -> 61.2 us, 256^3 FP32 580 ->
+    // 550 us against the chunks above; 2D rows measured the same either way)
+    L->zc_flat = L->dim == 2 || L->tuned ? zc : (gx * gy * L->NZ > 8192 ? 2 : 1);
     L->nparts = gx * gy * gz;
     // aux: kAuxHead doubles of scalars, then per-work-group partials (8 per group
     // of the fused kernel, 9 with a third composition; one per group of the Euler
@@ -301,6 +305,17 @@ void set_slots(const lbm_handle* h, KParams& kp, const char* src, char* dst) {
         kp.src_slot[s] = (src && used) ? src + h->L.slot_off[s] : nullptr;
         kp.dst_slot[s] = (dst && used) ? dst + h->L.slot_off[s] : nullptr;
     }
+}
+
+// launch of the fused kernel in one of its modes
+void launch_fused(const lbm_handle* h, int mode, KParams& kp, hipStream_t s) {
+    const bool step = mode == MODE_STEP || mode == MODE_STEP_PHI;
+    const bool flat = mode != MODE_DIAG && (h->L.qf == 0 || mode == MODE_SCALARS);
+    if (flat && !(step && kp.mean_subtract)) {
+        kp.zc = h->L.zc_flat;
+        kp.tiles_z = (kp.nz + kp.zc - 1) / kp.zc;
+    }
+    h->ks->fused(mode, dim3(unsigned(kp.tiles_x) * unsigned(kp.tiles_y) * unsigned(kp.tiles_z)), kp, s);
 }
 
 void fill_params(lbm_handle* h) {
@@ -630,7 +645,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     // walls on x and y: the fix-up kernel; z walls bounce back when the next step pulls
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
     for (int64_t i = 0; i < nsteps; ++i) {
-        h->ks->fused(MODE_STEP, h->L.grid, kp[h->cur], s);
+        launch_fused(h, MODE_STEP, kp[h->cur], s);
         for (int a = 0; a < 2; ++a)
             if (walls[a]) h->ks->walls(kp[h->cur], a, s);
         if (h->cfg.gravity_mean_subtract)
@@ -670,7 +685,8 @@ int lbm_moments(lbm_handle* h, uint32_t mask, void* const* out, int32_t out_dtyp
     }
     kp.mout_f32 = out_dtype == LBM_OUT_F32;
     if (mask) {
-        h->ks->fused(MODE_MOMENTS, h->L.grid, kp, s);
+        const uint32_t flow = LBM_M_P | LBM_M_UX | LBM_M_UY | LBM_M_UZ;
+        launch_fused(h, mask & flow ? MODE_MOMENTS : MODE_SCALARS, kp, s);
         if (int r = launched("moments kernel")) return r;
     }
     return LBM_OK;
@@ -707,7 +723,7 @@ int lbm_diagnostics(lbm_handle* h, double* host_out, void* stream) {
     KParams kp = h->base;
     set_slots(h, kp, h->copy[h->cur], nullptr);
     kp.mask_out = h->mask;
-    h->ks->fused(MODE_DIAG, h->L.grid, kp, s);
+    launch_fused(h, MODE_DIAG, kp, s);
     // 8 reductions (9 with a third composition: sum c^C goes to LBM_D_SUM_CC)
     launch_finalize(h->aux + kAuxHead, int(h->L.nparts), h->L.nc == 3 ? 9 : 8, 4, 1.0, h->aux + 8, s);
     // droplet count: Euler characteristic of the cells with phi >= 1/2, over the
@@ -820,7 +836,7 @@ int lbm_step_external(lbm_handle* h, const void* src, void* dst, void* phi_src, 
     kp.phi_ref = ref_in;
     // the buffered <phi> is recomputed with the mean subtraction, else carried over
     kp.ref_copy = h->cfg.gravity_mean_subtract ? nullptr : ref_out;
-    h->ks->fused(phi_src ? MODE_STEP_PHI : MODE_STEP, h->L.grid, kp, s);
+    launch_fused(h, phi_src ? MODE_STEP_PHI : MODE_STEP, kp, s);
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
     for (int a = 0; a < 2; ++a)
         if (walls[a]) h->ks->walls(kp, a, s);
@@ -838,7 +854,7 @@ int lbm_phase_field(lbm_handle* h, const void* state, void* phi, void* stream) {
     for (int i = 0; i < kNumMom; ++i) kp.mout[i] = nullptr;
     kp.mout[0] = phi;
     kp.mout_f32 = h->L.prec == LBM_FP64 ? 0 : 1;
-    h->ks->fused(MODE_MOMENTS, h->L.grid, kp, static_cast<hipStream_t>(stream));
+    launch_fused(h, MODE_SCALARS, kp, static_cast<hipStream_t>(stream));
     return launched("phase-field kernel");
 }
 

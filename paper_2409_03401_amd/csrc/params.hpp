@@ -19,7 +19,8 @@ constexpr int kNumDiag = 8;
 
 enum Prec : int { P64 = 0, P32 = 1, P16 = 2, PB16 = 3 };
 // MODE_STEP_PHI: a step that also writes phi of its source state (P.phi_out)
-enum Mode : int { MODE_STEP = 0, MODE_MOMENTS = 1, MODE_DIAG = 2, MODE_STEP_PHI = 3 };
+// MODE_SCALARS: moments other than pressure and velocity (they need neither f nor the stencil)
+enum Mode : int { MODE_STEP = 0, MODE_MOMENTS = 1, MODE_DIAG = 2, MODE_STEP_PHI = 3, MODE_SCALARS = 4 };
 // collision operator of the fused step: the paper's BGK, or two relaxation times
 // (flags): COLL_TRT two relaxation times, COLL_VD the variable-density flow model
 // COLL_GK general curvature matrices of the free energies (2 x 2 closure per node)
