@@ -228,12 +228,13 @@ __global__ void __launch_bounds__(NT) k_block(const KParams P, const BlockGeom B
         // the next collision writes spop: with flow the barrier after phi stands between
         if constexpr (!FLOW) __syncthreads();
     }
-    // the state after the last step, from this thread's own words
+    // the state after the last step, from this thread's own words (plain stores: the rows of a
+    // window end inside lines that its neighbours complete)
     if (owned) {
         each([&](auto s_, auto k_, auto) __attribute__((always_inline)) {
             constexpr int S = decltype(s_)::value;
-            if constexpr (decltype(k_)::value == 0) st_raw(dst(s_), idx, rest[SLOTS::field(S)]);
-            else st_raw(dst(s_), idx, spop[at(S) + tid]);
+            if constexpr (decltype(k_)::value == 0) st_raw<false>(dst(s_), idx, rest[SLOTS::field(S)]);
+            else st_raw<false>(dst(s_), idx, spop[at(S) + tid]);
         });
     }
 }

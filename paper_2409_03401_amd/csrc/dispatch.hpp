@@ -7,7 +7,7 @@ namespace lbm {
 
 struct KernelSet {
     // fused kernel in one of the modes (enum Mode)
-    void (*fused)(int mode, dim3 grid, const KParams& kp, hipStream_t s);
+    void (*fused)(int mode, bool gen, unsigned grid, const KParams& kp, hipStream_t s);
     // equilibrium initialisation, one thread per node (muC0: the third composition's
     // potential, families with three compositions only)
     void (*init)(const KParams& kp, const double* phi0, const double* muA0, const double* muB0,
@@ -25,17 +25,17 @@ struct KernelSet {
                            const double* muB0, hipStream_t s);
     // adjoint to (set = false) or from (set = true) an FP64 [slot][node] array
     void (*adj_copy)(const KParams& kp, int nslots, long long nodes, double* buf, bool set, hipStream_t s);
-    int tx, ty;  // work-group tile of the fused kernel
+    int nt;  // threads of the fused kernel: 2D the row segment, 3D the most nodes of a tile
     // several steps per launch on windows of nt nodes (2D; nullptr: no such kernel);
     // block_nt: the small and the large window
     void (*block)(int nt, unsigned grid, const KParams& kp, const BlockGeom& g, hipStream_t s);
     int block_nt[2];
 };
 
-// fluid: 0 (none) or 9 / 19; prec: Prec; (tx, ty): work-group tile, 0 for the
+// fluid: 0 (none) or 9 / 19; prec: Prec; tx: row segment of a 2D work-group, 0 for the
 // default.  nullptr for unsupported combinations.
 const KernelSet* kernels_2d(int fluid, int prec, int tx);
-const KernelSet* kernels_3d(int fluid, int prec, int tx, int ty);
+const KernelSet* kernels_3d(int fluid, int prec);
 // the paper's scalar lattices (D2Q9 / D3Q19 for g, h^A, h^B): all precisions, adjoint at FP64 / FP32
 const KernelSet* kernels_paper_2d(int fluid, int prec);
 const KernelSet* kernels_paper_3d(int fluid, int prec);

@@ -9,31 +9,40 @@
 
 namespace lbm {
 
-template <class SL, class FL, int PREC, int TX, int TY, bool ADJ = true, int COLL = COLL_BGK, int NC = 2>
+template <class SL, class FL, int PREC, int NT, bool ADJ = true, int COLL = COLL_BGK, int NC = 2>
 struct Family {
-    static void fused(int mode, dim3 grid, const KParams& kp, hipStream_t s) {
-        const dim3 block(TX, TY);
+    // the adjoint covers the ternary fluid (two compositions) at FP64 / FP32
+    static constexpr bool kAdj = ADJ && NC == 2 && (PREC == P32 || PREC == P64);
+    // gen: any grid, else rows of whole lines in 64 x 4 tiles (MODE_STEP; MODE_STEP_PHI of
+    // the families with an adjoint, whose recompute it serves)
+    static void fused(int mode, bool gen, unsigned grid, const KParams& kp, hipStream_t s) {
+        constexpr int CM = COLL & (COLL_VD | COLL_GK);  // what the moments depend on
+        const dim3 g(grid), block(NT);
         switch (mode) {
             case MODE_STEP:
-                hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP, PREC, TX, TY, COLL, NC>), grid, block, 0, s, kp);
+                if (gen) hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP, PREC, NT, true, COLL, NC>), g, block, 0, s, kp);
+                else hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP, PREC, NT, false, COLL, NC>), g, block, 0, s, kp);
                 break;
             case MODE_STEP_PHI:
+                if constexpr (kAdj)
+                    if (!gen) {
+                        hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP_PHI, PREC, NT, false, COLL>), g, block, 0, s, kp);
+                        break;
+                    }
                 if constexpr (NC == 2)
-                    hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP_PHI, PREC, TX, TY, COLL>), grid, block, 0, s, kp);
+                    hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP_PHI, PREC, NT, true, COLL>), g, block, 0, s, kp);
                 break;
             case MODE_SCALARS:
                 if constexpr (FL::Q > 0) {
-                    hipLaunchKernelGGL((k_lbm<SL, FL, MODE_SCALARS, PREC, TX, TY, (COLL & COLL_GK), NC>), grid, block, 0, s, kp);
+                    hipLaunchKernelGGL((k_lbm<SL, FL, MODE_SCALARS, PREC, NT, false, (COLL & COLL_GK), NC>), g, block, 0, s, kp);
                     break;
                 }
                 [[fallthrough]];
             case MODE_MOMENTS:
-                hipLaunchKernelGGL((k_lbm<SL, FL, MODE_MOMENTS, PREC, TX, TY, (COLL & (COLL_VD | COLL_GK)), NC>), grid,
-                                   block, 0, s, kp);
+                hipLaunchKernelGGL((k_lbm<SL, FL, MODE_MOMENTS, PREC, NT, false, CM, NC>), g, block, 0, s, kp);
                 break;
             default:
-                hipLaunchKernelGGL((k_lbm<SL, FL, MODE_DIAG, PREC, TX, TY, (COLL & (COLL_VD | COLL_GK)), NC>), grid,
-                                   block, 0, s, kp);
+                hipLaunchKernelGGL((k_lbm<SL, FL, MODE_DIAG, PREC, NT, false, CM, NC>), g, block, 0, s, kp);
                 break;
         }
     }
@@ -57,8 +66,6 @@ struct Family {
         const dim3 grid(unsigned((2 * face + 255) / 256));
         hipLaunchKernelGGL((k_walls<SL, FL, PREC, NC>), grid, dim3(256), 0, s, kp, axis);
     }
-    // the adjoint covers the ternary fluid (two compositions) at FP64 / FP32
-    static constexpr bool kAdj = ADJ && NC == 2 && (PREC == P32 || PREC == P64);
     static void adj_step(const KParams& kp, long long nodes, const void* phi, hipStream_t s) {
         if constexpr (kAdj)
             hipLaunchKernelGGL((k_adj_node<SL, FL, PREC>), dim3(unsigned((nodes + 255) / 256)), dim3(256), 0, s, kp,
@@ -90,7 +97,7 @@ struct Family {
         }
     }
     // the narrow row segments (LBM_TILE) march one step per launch
-    static constexpr bool kBlock = SL::DIM == 2 && TX == 256;
+    static constexpr bool kBlock = SL::DIM == 2 && NT == 256;
     static constexpr int kSmall = 256;
     static constexpr int large() {
         if constexpr (kBlock) return block_threads<SL, FL, PREC, COLL, NC>();
@@ -105,52 +112,52 @@ struct Family {
     static constexpr KernelSet set{&fused, &init, &get_pops, &set_pops, &walls,
                                    kAdj ? &adj_step : nullptr, kAdj ? &adj_seed : nullptr,
                                    kAdj ? &adj_gather : nullptr, kAdj ? &adj_init_local : nullptr,
-                                   kAdj ? &adj_copy : nullptr, TX, TY,
+                                   kAdj ? &adj_copy : nullptr, NT,
                                    kBlock ? &block : nullptr, {kBlock ? kSmall : 0, large()}};
 };
 
-template <class SL, class FL, int TX, int TY>
+template <class SL, class FL, int NT>
 const KernelSet* family_for_prec(int prec) {
     switch (prec) {
-        case P64: return &Family<SL, FL, P64, TX, TY>::set;
-        case P32: return &Family<SL, FL, P32, TX, TY>::set;
-        case P16: return &Family<SL, FL, P16, TX, TY>::set;
-        case PB16: return &Family<SL, FL, PB16, TX, TY>::set;
+        case P64: return &Family<SL, FL, P64, NT>::set;
+        case P32: return &Family<SL, FL, P32, NT>::set;
+        case P16: return &Family<SL, FL, P16, NT>::set;
+        case PB16: return &Family<SL, FL, PB16, NT>::set;
         default: return nullptr;
     }
 }
 
 // the TRT / MRT collisions, the variable-density model and general curvatures: all
 // four storage precisions, no adjoint
-template <class SL, class FL, int TX, int TY, int COLL = COLL_BGK>
+template <class SL, class FL, int NT, int COLL = COLL_BGK>
 const KernelSet* family_all_prec_noadj(int prec) {
     switch (prec) {
-        case P64: return &Family<SL, FL, P64, TX, TY, false, COLL>::set;
-        case P32: return &Family<SL, FL, P32, TX, TY, false, COLL>::set;
-        case P16: return &Family<SL, FL, P16, TX, TY, false, COLL>::set;
-        case PB16: return &Family<SL, FL, PB16, TX, TY, false, COLL>::set;
+        case P64: return &Family<SL, FL, P64, NT, false, COLL>::set;
+        case P32: return &Family<SL, FL, P32, NT, false, COLL>::set;
+        case P16: return &Family<SL, FL, P16, NT, false, COLL>::set;
+        case PB16: return &Family<SL, FL, PB16, NT, false, COLL>::set;
         default: return nullptr;
     }
 }
 
 // a third independent composition (N components): BGK Boussinesq step, all four
 // storage precisions, no adjoint
-template <class SL, class FL, int TX, int TY>
+template <class SL, class FL, int NT>
 const KernelSet* family_nc3(int prec) {
     switch (prec) {
-        case P64: return &Family<SL, FL, P64, TX, TY, false, COLL_BGK, 3>::set;
-        case P32: return &Family<SL, FL, P32, TX, TY, false, COLL_BGK, 3>::set;
-        case P16: return &Family<SL, FL, P16, TX, TY, false, COLL_BGK, 3>::set;
-        case PB16: return &Family<SL, FL, PB16, TX, TY, false, COLL_BGK, 3>::set;
+        case P64: return &Family<SL, FL, P64, NT, false, COLL_BGK, 3>::set;
+        case P32: return &Family<SL, FL, P32, NT, false, COLL_BGK, 3>::set;
+        case P16: return &Family<SL, FL, P16, NT, false, COLL_BGK, 3>::set;
+        case PB16: return &Family<SL, FL, PB16, NT, false, COLL_BGK, 3>::set;
         default: return nullptr;
     }
 }
 
 // one precision of a family without adjoint (for splitting large families over
 // translation units)
-template <class SL, class FL, int TX, int TY, int COLL, int PREC>
+template <class SL, class FL, int NT, int COLL, int PREC>
 const KernelSet* family_one_prec() {
-    return &Family<SL, FL, PREC, TX, TY, false, COLL>::set;
+    return &Family<SL, FL, PREC, NT, false, COLL>::set;
 }
 
 }  // namespace lbm

@@ -1,7 +1,8 @@
 // HIP kernels of the coupled lattice-Boltzmann step for gfx950.
 //
 // One fused kernel per (lattice family, mode, storage precision, tile).  A
-// work-group owns a TX x TY column of nodes and marches along z over `zc` planes.
+// work-group owns a column of nodes (3D: tile_x x tile_y, 2D: a row segment) and marches
+// along z over `zc` planes.
 // When the capillary force (or the free-energy diagnostic) needs grad phi and
 // lap phi, phi of three consecutive planes, each with a one-node ring, is staged
 // in LDS: the work-group computes phi of plane z+1 (its own nodes from registers
@@ -87,9 +88,6 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[N], int maxslot, 
 #ifndef LBM_NT_FLUID
 #define LBM_NT_FLUID 1
 #endif
-#ifndef LBM_FLAT_FILL
-#define LBM_FLAT_FILL 1
-#endif
 #ifndef LBM_FRAW
 #define LBM_FRAW 1
 #endif
@@ -129,8 +127,13 @@ constexpr int lbm_waves() {
     return LBM_WAVES_PER_EU;
 }
 
-template <class SL, class FL, int MODE, int PREC, int TX, int TY, int COLL = COLL_BGK, int NC = 2>
-__global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(lbm_waves<SL, PREC, COLL, NC, FL::Q>())))
+// GEN: any grid.  3D: the tile is P.tile_x x P.tile_y nodes, and a source copy with raw
+// populations at the x and y walls (P.raw_xy) bounces back there; stores are plain.
+// Otherwise 64 x 4 tiles (3D), exchanged copies, and non-temporal stores: the grids whose
+// rows are whole 128-byte lines.  The general kernel spends 20-60 scalar registers more
+// (spilled to vector lanes), 2-6 % on such a grid.
+template <class SL, class FL, int MODE, int PREC, int NT, bool GEN, int COLL = COLL_BGK, int NC = 2>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(lbm_waves<SL, PREC, COLL, NC, FL::Q>())))
 k_lbm(const KParams P) {
     using C = typename Stor<PREC>::C;
     using SLOTS = Slots<FL::Q, SL::Q, NC>;
@@ -141,11 +144,10 @@ k_lbm(const KParams P) {
     constexpr bool HAS_Y = SL::DIM == 3;
     using NODE = Node<SL, FL, PREC, COLL, NC>;
     using STL = typename NODE::STL;
-    constexpr int LX = TX + 2;
-    constexpr int LY = HAS_Y ? TY + 2 : 1;
-    constexpr int OY = HAS_Y ? 1 : 0;
+    // 3D: a tile of up to NT nodes (GEN: P.tile_x x P.tile_y, lbm_api.hip); 2D: a row
+    // segment of NT nodes
     constexpr int NSLOT = STENCIL ? 3 : 1;
-    constexpr int NT = TX * TY;
+    constexpr int CELLS = HAS_Y ? (GEN ? kTileCells : (kTileX + 2) * (kTileY + 2)) : NT + 2;  // phi of a tile and its ring
     constexpr int G0 = SLOTS::G0, A0 = SLOTS::A0, B0 = SLOTS::B0, HC0 = SLOTS::C0;
     // NC = 3: a third independent composition C (N components), BGK Boussinesq step
     constexpr bool NC3 = NC == 3;
@@ -154,7 +156,6 @@ k_lbm(const KParams P) {
     static_assert(SLOTS::N <= kMaxSlots, "slot table too small for this lattice family");
     constexpr bool VD = NODE::VD;
     constexpr bool GK = NODE::GK;
-    static_assert(TY == 1 || HAS_Y, "2D problems use one row per work-group");
     // the private LDS ring of scalar populations, unless it would not leave room for a
     // second work-group per compute unit (the paper's D3Q19 scalar lattice in FP32 / FP64,
     // and with the general-curvature collision or MRT with FP16).  The other D3Q19
@@ -164,7 +165,7 @@ k_lbm(const KParams P) {
                                                2 * (1 + NC) * QS * NT * sizeof(C) <= 96 * 1024);
     static_assert((QS - 1) % 2 == 0, "moving directions come in opposite pairs");
 
-    __shared__ C sphi[NSLOT][LY][LX];
+    __shared__ C sphi[NSLOT][CELLS];
     // this thread's own scalar populations of the current and the next plane
     // (thread-private ring of two planes, [plane][word][thread], no barriers needed).
     // FP32 / FP64: one word per population.  16-bit storage (PACKED): per field, the
@@ -178,16 +179,37 @@ k_lbm(const KParams P) {
     using W = typename std::conditional<PACKED, unsigned, C>::type;
     __shared__ W spop[(STENCIL && LDS_POPS) ? 2 : 1][(STENCIL && LDS_POPS) ? NWORD : 1][(STENCIL && LDS_POPS) ? NT : 1];
 
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    const int tid = ty * TX + tx;
+    const int tid = threadIdx.x;
+    const int tw = HAS_Y ? (GEN ? P.tile_x : kTileX) : NT, th = HAS_Y ? (GEN ? P.tile_y : kTileY) : 1;
+    const int lx = tw + 2;  // a row of phi with its ring
+    // lanes beyond the tile repeat its last row (nothing of theirs is stored)
+    const int row = HAS_Y ? (GEN ? (tid * P.tile_inv) >> 16 : tid / kTileX) : 0;
+    const int tx = tid - row * tw, ty = GEN ? min(row, th - 1) : row;
     // tile of this work-group: x fastest, then y, then the z chunk
     const int tile = xcd_tile(blockIdx.x, P.tiles_x * P.tiles_y * P.tiles_z);
     const int bx = tile % P.tiles_x;
     const int by = (tile / P.tiles_x) % P.tiles_y;
     const int bz = tile / (P.tiles_x * P.tiles_y);
-    const int x = bx * TX + tx;
-    const int y = by * TY + ty;
-    const bool active = (x < P.nx) && (y < P.ny);
+    const int x = bx * tw + tx;
+    const int y = by * th + ty;
+    const bool active = (!GEN || row < th) && (x < P.nx) && (y < P.ny);
+    const int cell = HAS_Y ? (ty + 1) * lx + tx + 1 : tx + 1;  // phi of this node in sphi
+    // the source copy holds raw populations at the x and y walls and this tile or its ring
+    // touches one: its pulls bounce back there (a second variant of the loads)
+    const bool edge = HAS_Y && GEN && P.raw_xy &&
+                      ((P.wall_x && (bx * tw <= 1 || (bx + 1) * tw >= P.nx - 1)) ||
+                       (P.wall_y && (by * th <= 1 || (by + 1) * th >= P.ny - 1)));
+    // does the pull of a population moving along (ex, ey, ez) at node (xx, yy, .) bounce back:
+    // at a z wall (zlo / zhi, wave-uniform), or at an x or y wall of a raw copy (per lane)?
+    auto bounces = [&](auto ex_, auto ey_, auto ez_, bool zlo, bool zhi, int xx, int yy)
+                       __attribute__((always_inline)) -> bool {
+        constexpr int ex = decltype(ex_)::value, ey = decltype(ey_)::value;
+        bool b = false;
+        if constexpr (ex != 0) b = P.wall_x && xx == (ex > 0 ? 0 : P.nx - 1);
+        if constexpr (ey != 0) b = b || (P.wall_y && yy == (ey > 0 ? 0 : P.ny - 1));
+        return (HAS_Y && GEN && P.raw_xy && b) || zbounce<decltype(ez_)::value>(zlo, zhi);
+    };
+
     const int z0 = bz * P.zc;
     const int z1 = min(z0 + P.zc, P.nz);
 
@@ -231,35 +253,44 @@ k_lbm(const KParams P) {
     auto load_once = [&](auto s_, auto k_, auto lat_, unsigned idx) __attribute__((always_inline)) -> C {
         constexpr int S = decltype(s_)::value;
         using L = typename decltype(lat_)::type;
-        constexpr bool NT = LBM_NT_FLUID && SL::DIM == 3 && L::ex(decltype(k_)::value) == 0;
-        return ld_at<PREC, SLOTS::rest(S), NT>(src(s_), idx, wref_dec(s_, k_, lat_), P.finv[SLOTS::field(S)]);
+        constexpr bool ONCE = LBM_NT_FLUID && SL::DIM == 3 && L::ex(decltype(k_)::value) == 0;
+        return ld_at<PREC, SLOTS::rest(S), ONCE>(src(s_), idx, wref_dec(s_, k_, lat_), P.finv[SLOTS::field(S)]);
     };
-    // scalar populations arriving at node idx (pull from idx - e_k; the node's own
-    // opposite population where that crosses a z wall: zlo / zhi, wave-uniform)
+    // scalar populations arriving at node idx (pull from idx - e_k; the node's own opposite
+    // population where that crosses a z wall: zlo / zhi, wave-uniform).  GEN: bounce_pops
+    // replaces those that bounce back at any wall (a branch that only planes and tiles at a
+    // wall take, its loads in the same batch)
     // The scalar populations of a node in their stored form (RAW: 16-bit storage keeps
     // the bits of the moving populations and of the FP32 rest population, decoded later;
     // FP32 / FP64 the values), field-major: g, hA, hB (, hC), QS each
     constexpr bool RAW16 = PREC == P16 || PREC == PB16;
     constexpr int NSC = (1 + NC) * QS;
     using RW = typename std::conditional<RAW16, unsigned, C>::type;
+    auto one_pop = [&](auto s_, unsigned t) __attribute__((always_inline)) -> RW {
+        constexpr int S = decltype(s_)::value;
+        if constexpr (!RAW16) return ld_at<PREC, SLOTS::rest(S)>(src(s_), t, 0.0f, 1.0f);
+        else if constexpr (SLOTS::rest(S)) return __builtin_bit_cast(unsigned, ld_at<PREC, true>(src(s_), t, 0.0f, 1.0f));
+        else return *reinterpret_cast<const unsigned short*>(src(s_) + t * 2u);
+    };
+    // every field's population k from slot kk at node t
+    auto pops_at = [&](auto k_, auto kk_, unsigned t, RW (&raw)[NSC]) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_)::value, kk = decltype(kk_)::value;
+        raw[k] = one_pop(IC<G0 + kk>{}, t);
+        raw[QS + k] = one_pop(IC<A0 + kk>{}, t);
+        raw[2 * QS + k] = one_pop(IC<B0 + kk>{}, t);
+        if constexpr (NC3) raw[3 * QS + k] = one_pop(IC<HC0 + kk>{}, t);
+    };
     auto load_pops = [&](unsigned idx, const Nbr& nb, bool zlo, bool zhi, RW (&raw)[NSC]) __attribute__((always_inline)) {
-        auto one = [&](auto s_, auto k_, unsigned t) __attribute__((always_inline)) -> RW {
-            constexpr int S = decltype(s_)::value;
-            if constexpr (!RAW16) return ld_at<PREC, SLOTS::rest(S)>(src(s_), t, 0.0f, 1.0f);
-            else if constexpr (SLOTS::rest(S)) return __builtin_bit_cast(unsigned, ld_at<PREC, true>(src(s_), t, 0.0f, 1.0f));
-            else return *reinterpret_cast<const unsigned short*>(src(s_) + t * 2u);
-        };
         static_for<0, QS>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value, o = SL::opp(k);
-            auto fields = [&](auto kk_, unsigned t) __attribute__((always_inline)) {
-                constexpr int kk = decltype(kk_)::value;
-                raw[k] = one(IC<G0 + kk>{}, kk_, t);
-                raw[QS + k] = one(IC<A0 + kk>{}, kk_, t);
-                raw[2 * QS + k] = one(IC<B0 + kk>{}, kk_, t);
-                if constexpr (NC3) raw[3 * QS + k] = one(IC<HC0 + kk>{}, kk_, t);
-            };
-            if (zbounce<SL::ez(k)>(zlo, zhi)) fields(IC<o>{}, idx);
-            else fields(kc, unsigned(int(idx) + pull_offset<SL::ex(k), SL::ey(k), SL::ez(k)>(nb)));
+            if (!GEN && zbounce<SL::ez(k)>(zlo, zhi)) pops_at(kc, IC<o>{}, idx, raw);
+            else pops_at(kc, kc, unsigned(int(idx) + pull_offset<SL::ex(k), SL::ey(k), SL::ez(k)>(nb)), raw);
+        });
+    };
+    auto bounce_pops = [&](unsigned idx, bool zlo, bool zhi, int xx, int yy, RW (&raw)[NSC]) __attribute__((always_inline)) {
+        static_for<1, QS>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value, o = SL::opp(k);
+            if (bounces(IC<SL::ex(k)>{}, IC<SL::ey(k)>{}, IC<SL::ez(k)>{}, zlo, zhi, xx, yy)) pops_at(kc, IC<o>{}, idx, raw);
         });
     };
     // decoded values of one field (base slot B, first raw entry R0)
@@ -284,6 +315,7 @@ k_lbm(const KParams P) {
                             __attribute__((always_inline)) {
         RW raw[NSC];
         load_pops(idx, nb, zlo, zhi, raw);
+        if (GEN && (zlo || zhi || edge)) bounce_pops(idx, zlo, zhi, x, y, raw);
         decode_pops(raw, gg, aa, bb, qq);
         NODE::pop_sums(gg, aa, bb, qq, phis, cA, cB, cC);
     };
@@ -305,10 +337,6 @@ k_lbm(const KParams P) {
     C cg[QS], ca[QS], cb[QS], ng[QS], na[QS], nb[QS], cq[QC], nq[QC];
     double c_ps = 0.0, c_cA = 0.0, c_cB = 0.0, n_ps = 0.0, n_cA = 0.0, n_cB = 0.0, c_cC = 0.0, n_cC = 0.0;
 
-    // phi of plane zz (tile + ring) into LDS slot `slot`; this thread's own node
-    // populations go to the private LDS ring entry `pbuf` when the node is inside.
-    // A z wall plane takes the bounce-back pulls (a separate, uniform branch: the
-    // interior planes keep the plain loads)
     // PACKED: this node's own scalar populations (stored form) into the LDS ring (per
     // field: the FP32 rest population, then the moving populations of k and opp(k) in one
     // word) and their zeroth moments (the moving populations summed as moving_sum does)
@@ -346,6 +374,7 @@ k_lbm(const KParams P) {
                            double& cB, double& cC) __attribute__((always_inline)) {
         RW raw[NSC];
         load_pops(idx, nb, zlo, zhi, raw);
+        if (GEN && (zlo || zhi)) bounce_pops(idx, zlo, zhi, x, y, raw);
         finish_packed(raw, pbuf, phis, cA, cB, cC);
     };
 
@@ -354,27 +383,34 @@ k_lbm(const KParams P) {
     // repeat its last node) in one basic block, so that all loads go out together; only
     // the waves that hold ring nodes decode them (a wave-uniform branch).  The stores
     // need no conditions: a lane's private LDS ring entries and the phi cells of lanes
-    // outside the domain are never read, and a repeated ring node writes the same value
-    // to the same cell.
-    auto fill_body_flat = [&](int zm, bool zlo, bool zhi, int slot, int pbuf, double& ps, double& cA, double& cB,
-                              double& cC) __attribute__((always_inline)) {
-        constexpr int NH = 2 * LX + 2 * TY;
+    // outside the domain are never read, and a repeated node writes the same value to the
+    // same cell.
+    const int NH = 2 * lx + 2 * th;
+    auto ring_cell = [&](int& hx, int& hy) __attribute__((always_inline)) {
+        const int i = min(tid, NH - 1);
+        if (i < lx) { hx = i; hy = 0; }
+        else if (i < 2 * lx) { hx = i - lx; hy = th + 1; }
+        else if (i < 2 * lx + th) { hx = 0; hy = i - 2 * lx + 1; }
+        else { hx = lx - 1; hy = i - 2 * lx - th + 1; }
+    };
+    auto fill_load = [&](int zm, bool zlo, bool zhi, RW (&own)[NSC], RW (&ring)[NSC])
+                         __attribute__((always_inline)) {
         static_assert(NT % 64 == 0, "whole waves");
         const int ox = map_coord(min(x, P.nx), P.nx, P.wall_x), oy = map_coord(min(y, P.ny), P.ny, P.wall_y);
-        const int i = min(tid, NH - 1);
         int hx, hy;
-        if (i < LX) { hx = i; hy = 0; }
-        else if (i < 2 * LX) { hx = i - LX; hy = TY + 1; }
-        else if (i < 2 * LX + TY) { hx = 0; hy = i - 2 * LX + 1; }
-        else { hx = LX - 1; hy = i - 2 * LX - TY + 1; }
-        const int rx = map_coord(min(bx * TX + hx - 1, P.nx), P.nx, P.wall_x);
-        const int ry = map_coord(min(by * TY + hy - 1, P.ny), P.ny, P.wall_y);
-        RW own[NSC], ring[NSC];
-        load_pops(unsigned((zm * P.ny + oy) * P.nx + ox), neighbours(ox, oy, zm, P), zlo, zhi, own);
-        load_pops(unsigned((zm * P.ny + ry) * P.nx + rx), neighbours(rx, ry, zm, P), zlo, zhi, ring);
-        // keep the scheduler from moving the decode and sums of the own node between the
-        // loads (it would then wait for them before the ring loads go out)
-        __builtin_amdgcn_sched_barrier(0);
+        ring_cell(hx, hy);
+        const int rx = map_coord(min(bx * tw + hx - 1, P.nx), P.nx, P.wall_x);
+        const int ry = map_coord(min(by * th + hy - 1, P.ny), P.ny, P.wall_y);
+        const unsigned oi = unsigned((zm * P.ny + oy) * P.nx + ox), ri = unsigned((zm * P.ny + ry) * P.nx + rx);
+        load_pops(oi, neighbours(ox, oy, zm, P), zlo, zhi, own);
+        load_pops(ri, neighbours(rx, ry, zm, P), zlo, zhi, ring);
+        if (GEN && (zlo || zhi || edge)) {
+            bounce_pops(oi, zlo, zhi, ox, oy, own);
+            bounce_pops(ri, zlo, zhi, rx, ry, ring);
+        }
+    };
+    auto fill_finish = [&](const RW (&own)[NSC], const RW (&ring)[NSC], int slot, int pbuf, double& ps, double& cA,
+                           double& cB, double& cC) __attribute__((always_inline)) {
         if constexpr (PACKED) {
             finish_packed(own, pbuf, ps, cA, cB, cC);
         } else if constexpr (LDS_POPS) {
@@ -392,31 +428,29 @@ k_lbm(const KParams P) {
             decode_pops(own, ng, na, nb, nq);
             NODE::pop_sums(ng, na, nb, nq, ps, cA, cB, cC);
         }
-        sphi[slot][ty + OY][tx + 1] = C(phi_from(ps, cA, cB, cC));
+        sphi[slot][cell] = C(phi_from(ps, cA, cB, cC));
         // the first lane of this wave holds a ring node (wave-uniform)
         if (__builtin_amdgcn_readfirstlane(tid) < NH) {
             C tg[QS], ta[QS], tb[QS], tq[QC];
             double rps, rsa, rsb, rsc;
+            int hx, hy;
+            ring_cell(hx, hy);
             decode_pops(ring, tg, ta, tb, tq);
             NODE::pop_sums(tg, ta, tb, tq, rps, rsa, rsb, rsc);
-            sphi[slot][hy][hx] = C(phi_from(rps, rsa, rsb, rsc));
+            sphi[slot][hy * lx + hx] = C(phi_from(rps, rsa, rsb, rsc));
         }
     };
 
-    auto fill_body = [&](int zm, bool zlo, bool zhi, int slot, int pbuf, double& ps, double& cA, double& cB,
-                         double& cC) __attribute__((always_inline)) {
-        if constexpr (HAS_Y && LBM_FLAT_FILL) {
-            fill_body_flat(zm, zlo, zhi, slot, pbuf, ps, cA, cB, cC);
-            return;
-        }
+    // 2D: a row segment and the nodes on both sides of it
+    auto fill_row = [&](int zm, bool zlo, bool zhi, int slot, int pbuf, double& ps, double& cA, double& cB,
+                        double& cC) __attribute__((always_inline)) {
         if (active) {
             if constexpr (PACKED) {
-                fill_packed(unsigned((zm * P.ny + y) * P.nx + x), neighbours(x, y, zm, P), zlo, zhi, pbuf, ps, cA, cB,
-                            cC);
+                fill_packed(unsigned(zm * P.nx + x), neighbours(x, 0, zm, P), zlo, zhi, pbuf, ps, cA, cB, cC);
             } else if constexpr (LDS_POPS) {
                 C gg[QS], aa[QS], bb[QS], qq[QC];
-                load_scalars(unsigned((zm * P.ny + y) * P.nx + x), neighbours(x, y, zm, P), zlo, zhi, gg, aa, bb,
-                             qq, ps, cA, cB, cC);
+                load_scalars(unsigned(zm * P.nx + x), neighbours(x, 0, zm, P), zlo, zhi, gg, aa, bb, qq, ps, cA,
+                             cB, cC);
 #pragma unroll
                 for (int k = 0; k < QS; ++k) {
                     spop[pbuf][k][tid] = gg[k];
@@ -425,39 +459,44 @@ k_lbm(const KParams P) {
                     if constexpr (NC3) spop[pbuf][3 * QS + k][tid] = qq[k];
                 }
             } else {
-                load_scalars(unsigned((zm * P.ny + y) * P.nx + x), neighbours(x, y, zm, P), zlo, zhi, ng, na, nb,
-                             nq, ps, cA, cB, cC);
+                load_scalars(unsigned(zm * P.nx + x), neighbours(x, 0, zm, P), zlo, zhi, ng, na, nb, nq, ps, cA,
+                             cB, cC);
             }
-            sphi[slot][ty + OY][tx + 1] = C(phi_from(ps, cA, cB, cC));
-        } else if (x <= P.nx && y <= P.ny) {
-            // ghost column / row just beyond the domain edge
-            sphi[slot][ty + OY][tx + 1] = node_phi(map_coord(x, P.nx, P.wall_x),
-                                                   HAS_Y ? map_coord(y, P.ny, P.wall_y) : 0, zm, zlo, zhi);
+            sphi[slot][cell] = C(phi_from(ps, cA, cB, cC));
+        } else if (x <= P.nx) {
+            // ghost column just beyond the domain edge
+            sphi[slot][cell] = node_phi(map_coord(x, P.nx, P.wall_x), 0, zm, zlo, zhi);
         }
-        constexpr int NH = HAS_Y ? 2 * LX + 2 * TY : 2;
-        for (int i = tid; i < NH; i += NT) {
-            int hx, hy;
-            if constexpr (HAS_Y) {
-                if (i < LX) { hx = i; hy = 0; }
-                else if (i < 2 * LX) { hx = i - LX; hy = TY + 1; }
-                else if (i < 2 * LX + TY) { hx = 0; hy = i - 2 * LX + 1; }
-                else { hx = LX - 1; hy = i - 2 * LX - TY + 1; }
-            } else {
-                hx = (i == 0) ? 0 : LX - 1;
-                hy = 0;
-            }
-            const int gx = bx * TX + hx - 1;
-            const int gy = HAS_Y ? by * TY + hy - 1 : 0;
-            if (gx > P.nx || gy > P.ny) continue;  // beyond the ghost layer: never read
-            sphi[slot][hy][hx] = node_phi(map_coord(gx, P.nx, P.wall_x),
-                                          HAS_Y ? map_coord(gy, P.ny, P.wall_y) : 0, zm, zlo, zhi);
+        for (int i = tid; i < 2; i += NT) {
+            const int hx = (i == 0) ? 0 : lx - 1;
+            const int gx = bx * tw + hx - 1;
+            if (gx > P.nx) continue;  // beyond the ghost layer: never read
+            sphi[slot][hx] = node_phi(map_coord(gx, P.nx, P.wall_x), 0, zm, zlo, zhi);
+        }
+    };
+
+    // phi of plane zz (tile + ring) into LDS slot `slot`; this thread's own node populations
+    // go to the private LDS ring entry `pbuf`
+    auto fill_body = [&](int zm, bool zlo, bool zhi, int slot, int pbuf, double& ps, double& cA, double& cB,
+                         double& cC) __attribute__((always_inline)) {
+        if constexpr (HAS_Y) {
+            RW own[NSC], ring[NSC];
+            fill_load(zm, zlo, zhi, own, ring);
+            // keep the scheduler from moving the decode and sums of the own node between the
+            // loads (it would then wait for them before the ring loads go out)
+            __builtin_amdgcn_sched_barrier(0);
+            fill_finish(own, ring, slot, pbuf, ps, cA, cB, cC);
+        } else {
+            fill_row(zm, zlo, zhi, slot, pbuf, ps, cA, cB, cC);
         }
     };
     auto fill_plane = [&](int zz, int slot, int pbuf, double& ps, double& cA, double& cB, double& cC)
                           __attribute__((always_inline)) {
         const int zm = map_coord(zz, P.nz, P.wall_z);
         const bool zlo = P.wall_z && zm == 0, zhi = P.wall_z && zm == P.nz - 1;
-        if (zlo || zhi) fill_body(zm, zlo, zhi, slot, pbuf, ps, cA, cB, cC);
+        // not GEN: a z wall plane is a separate, uniform branch, and the interior planes keep
+        // the plain loads
+        if (GEN || zlo || zhi) fill_body(zm, zlo, zhi, slot, pbuf, ps, cA, cB, cC);
         else fill_body(zm, false, false, slot, pbuf, ps, cA, cB, cC);
     };
 
@@ -537,27 +576,26 @@ k_lbm(const KParams P) {
         // moments need them, so that no wait for them sits before the plane fill's loads
         constexpr bool FRAW = LBM_FRAW && (PREC == P16 || PREC == PB16);
         unsigned fraw[(QF > 0 && FRAW) ? QF : 1];
+        auto one_f = [&](auto kc, auto from_, unsigned t) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            if constexpr (FRAW && k != 0) {
+                constexpr bool ONCE = LBM_NT_FLUID && SL::DIM == 3 && FL::ex(k) == 0;
+                fraw[k] = ld_raw<unsigned short, ONCE>(reinterpret_cast<const unsigned short*>(src(from_) + t * 2u));
+            } else {
+                fpop[k] = load_once(from_, from_, FLT{}, t);
+            }
+        };
         auto load_f_body = [&](bool zlo, bool zhi) __attribute__((always_inline)) {
             static_for<0, QF>([&](auto kc) __attribute__((always_inline)) {
-                constexpr int k = decltype(kc)::value, o = FL::opp(k);
-                if constexpr (FRAW && k != 0) {
-                    constexpr bool NT = LBM_NT_FLUID && SL::DIM == 3 && FL::ex(k) == 0;
-                    const char* base;
-                    unsigned t;
-                    if (zbounce<FL::ez(k)>(zlo, zhi)) {
-                        base = src(IC<o>{});
-                        t = idx;
-                    } else {
-                        base = src(kc);
-                        t = unsigned(int(idx) + pull_offset<FL::ex(k), FL::ey(k), FL::ez(k)>(nbr));
-                    }
-                    fraw[k] = ld_raw<unsigned short, NT>(reinterpret_cast<const unsigned short*>(base + t * 2u));
-                } else if (zbounce<FL::ez(k)>(zlo, zhi)) {
-                    fpop[k] = load_once(IC<o>{}, IC<o>{}, FLT{}, idx);
-                } else {
-                    const unsigned src_idx = unsigned(int(idx) + pull_offset<FL::ex(k), FL::ey(k), FL::ez(k)>(nbr));
-                    fpop[k] = load_once(kc, kc, FLT{}, src_idx);
-                }
+                constexpr int k = decltype(kc)::value;
+                if (!GEN && zbounce<FL::ez(k)>(zlo, zhi)) one_f(kc, IC<FL::opp(k)>{}, idx);
+                else one_f(kc, kc, unsigned(int(idx) + pull_offset<FL::ex(k), FL::ey(k), FL::ez(k)>(nbr)));
+            });
+        };
+        auto bounce_f = [&](bool zlo, bool zhi) __attribute__((always_inline)) {
+            static_for<1, QF>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int k = decltype(kc)::value;
+                if (bounces(IC<FL::ex(k)>{}, IC<FL::ey(k)>{}, IC<FL::ez(k)>{}, zlo, zhi, x, y)) one_f(kc, IC<FL::opp(k)>{}, idx);
             });
         };
         // 16-bit storage: z-wall bounce-back by selecting the source slot and node (no
@@ -571,7 +609,7 @@ k_lbm(const KParams P) {
             static_for<0, QF>([&](auto kc) __attribute__((always_inline)) {
                 constexpr int k = decltype(kc)::value, o = FL::opp(k);
                 if constexpr (k != 0) {
-                    constexpr bool NT = LBM_NT_FLUID && SL::DIM == 3 && FL::ex(k) == 0;
+                    constexpr bool ONCE = LBM_NT_FLUID && SL::DIM == 3 && FL::ex(k) == 0;
                     const unsigned pulled = unsigned(int(fidx) + pull_offset<FL::ex(k), FL::ey(k), FL::ez(k)>(fnb));
                     const char* base = src(kc);
                     unsigned t = pulled;
@@ -580,7 +618,7 @@ k_lbm(const KParams P) {
                         base = b ? src(IC<o>{}) : base;
                         t = b ? fidx : pulled;
                     }
-                    fraw[k] = ld_raw<unsigned short, NT>(reinterpret_cast<const unsigned short*>(base + t * 2u));
+                    fraw[k] = ld_raw<unsigned short, ONCE>(reinterpret_cast<const unsigned short*>(base + t * 2u));
                 } else {
                     fpop[0] = load_once(kc, kc, FLT{}, fidx);
                 }
@@ -588,12 +626,14 @@ k_lbm(const KParams P) {
         };
         auto load_f = [&]() __attribute__((always_inline)) {
             if constexpr (FLOW) {
-                if constexpr (FRAW && HAS_Y && LBM_FLAT_FILL) {
+                const bool zlo = P.wall_z && z == 0, zhi = P.wall_z && z == P.nz - 1;
+                if constexpr (FRAW && HAS_Y) {
                     load_f_sel();  // every lane loads (lanes outside the domain: in-range stand-ins)
+                    if (GEN && edge && active) bounce_f(zlo, zhi);
                 } else if (active) {
-                    const bool zlo = P.wall_z && z == 0, zhi = P.wall_z && z == P.nz - 1;
-                    if (zlo || zhi) load_f_body(zlo, zhi);
+                    if (GEN || zlo || zhi) load_f_body(zlo, zhi);
                     else load_f_body(false, false);
+                    if (GEN && (zlo || zhi || edge)) bounce_f(zlo, zhi);
                 }
             }
         };
@@ -610,7 +650,7 @@ k_lbm(const KParams P) {
         } else {
             if (active) {
                 const bool zlo = P.wall_z && z == 0, zhi = P.wall_z && z == P.nz - 1;
-                if (zlo || zhi) load_scalars(idx, nbr, zlo, zhi, cg, ca, cb, cq, c_ps, c_cA, c_cB, c_cC);
+                if (GEN || zlo || zhi) load_scalars(idx, nbr, zlo, zhi, cg, ca, cb, cq, c_ps, c_cA, c_cB, c_cC);
                 else load_scalars(idx, nbr, false, false, cg, ca, cb, cq, c_ps, c_cA, c_cB, c_cC);
             }
         }
@@ -631,9 +671,9 @@ k_lbm(const KParams P) {
                 NODE::stencil(
                     [&](auto ex_, auto ey_, auto ez_) __attribute__((always_inline)) -> C {
                         constexpr int ex = decltype(ex_)::value, ey = decltype(ey_)::value, ez = decltype(ez_)::value;
-                        return sphi[ez == 0 ? sc : (ez > 0 ? sp : sm)][ty + OY + ey][tx + 1 + ex];
+                        return sphi[ez == 0 ? sc : (ez > 0 ? sp : sm)][cell + ey * lx + ex];
                     },
-                    sphi[sc][ty + OY][tx + 1], grad, lap);
+                    sphi[sc][cell], grad, lap);
             }
 
             C u[3] = {C(0), C(0), C(0)};
@@ -656,7 +696,7 @@ k_lbm(const KParams P) {
 
                 // post-collision populations go to this node's own slots of the other copy
                 NODE::collide(P, fpop, g, a, b, cq, c_ps, sA, sB, sC, m, muC, phi, F, u, p_h, irho,
-                              [&](auto s_, auto v) __attribute__((always_inline)) { st_raw(dst(s_), idx, v); });
+                              [&](auto s_, auto v) __attribute__((always_inline)) { st_raw<!GEN>(dst(s_), idx, v); });
             } else if constexpr (MODE == MODE_MOMENTS || MODE == MODE_SCALARS) {
                 // hydrodynamic pressure: p_h, or rho c_s^2 p* with variable density
                 const double p_out = VD && FLOW ? double(p_h) / (3.0 * double(irho)) : double(p_h);

@@ -9,9 +9,9 @@ namespace lbm {
 template <class FL>
 static const KernelSet* by_tile(int prec, int tx) {
     switch (tx) {
-        case 64: return family_for_prec<D2Q5K, FL, 64, 1>(prec);
-        case 128: return family_for_prec<D2Q5K, FL, 128, 1>(prec);
-        default: return family_for_prec<D2Q5K, FL, 256, 1>(prec);
+        case 64: return family_for_prec<D2Q5K, FL, 64>(prec);
+        case 128: return family_for_prec<D2Q5K, FL, 128>(prec);
+        default: return family_for_prec<D2Q5K, FL, 256>(prec);
     }
 }
 

@@ -1,18 +1,12 @@
-// 3D lattice families (D3Q7 scalars, optional D3Q19 fluid) with 64 x 4 node
-// columns per work-group (32 x 8 on request).
+// 3D lattice families (D3Q7 scalars, optional D3Q19 fluid), 256-node columns per
+// work-group.
 #include "family.hpp"
 
 namespace lbm {
 
-template <class FL>
-static const KernelSet* by_tile(int prec, int tx, int ty) {
-    if (tx == 32 && ty == 8) return family_for_prec<D3Q7K, FL, 32, 8>(prec);
-    return family_for_prec<D3Q7K, FL, 64, 4>(prec);
-}
-
-const KernelSet* kernels_3d(int fluid, int prec, int tx, int ty) {
-    if (fluid == 0) return by_tile<NoLattice>(prec, tx, ty);
-    if (fluid == 19) return by_tile<D3Q19K>(prec, tx, ty);
+const KernelSet* kernels_3d(int fluid, int prec) {
+    if (fluid == 0) return family_for_prec<D3Q7K, NoLattice, kTileNodes>(prec);
+    if (fluid == 19) return family_for_prec<D3Q7K, D3Q19K, kTileNodes>(prec);
     return nullptr;
 }
 

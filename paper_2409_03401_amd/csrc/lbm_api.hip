@@ -34,6 +34,12 @@ constexpr size_t kAlign = 256;
 constexpr int kAuxHead = 32;
 size_t round_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
+// work-groups of the fused kernel: tiles of tx x ty nodes in chunks of zc planes
+struct Tiles {
+    int tx, ty, zc, gx, gy, gz;
+    long long groups() const { return (long long)gx * gy * gz; }
+};
+
 struct Layout {
     const KernelSet* ks;
     int dim, qf, qs, nslots, prec;
@@ -43,10 +49,12 @@ struct Layout {
     size_t slot_off[kMaxSlots];
     size_t copy_bytes;
     size_t stride_m, stride_r;  // bytes of a moving / rest slot
-    int tx, ty, zc;
-    bool tuned;  // the environment chooses the tile or the chunk length
-    int tiles[3];
-    int zc_flat;      // chunk length of the kernels without the phi stencil
+    bool tuned;   // the environment chooses the tile or the chunk length
+    bool whole;   // every row of a slot is whole 128-byte lines
+    Tiles line;   // 64 x 4 tiles in 3D, row segments in 2D
+    Tiles gen;    // of the general kernel: a tile shape chosen for the grid (3D)
+    bool gen_steps;  // steps go through the general kernel
+    int zc_flat;  // chunk length of the kernels without the phi stencil
     long long nparts;     // work-groups of the fused kernel
     size_t aux_bytes;
     size_t mask_off;  // diagnostics mask (1 byte per node) after the aux area
@@ -58,6 +66,80 @@ struct Layout {
     size_t adj_state_bytes, adj_scratch_bytes;  // the two parts of adj_bytes
     long long adj_parts;
 };
+
+// Tile of a 3D work-group of the general kernel: (tx, ty) when given and possible, else
+// chosen for the grid.  Equal tiles across x (a narrow last tile runs ahead of its
+// neighbours and loses the phi ring that they share in L2: 297 x 182 x 133 FP32 624 us a
+// step with five 60 x 4 tiles a row, 722 with 64 x 4), at least 48 nodes wide (narrower rows
+// touch a line for every few nodes: 144 x 130 x 120 FP32 180 us with 48 x 5 tiles, 253 with
+// 36 x 7) or whole lines (96^3 FP32: 32 x 8 60 us, 64 x 4 and 96 x 2 65), and among those
+// the fewest tiles, weighed with the lines that a tile's rows and ring touch (100 x 75 x 50
+// FP16: 50 x 5 28.1 us, 100 x 2 28.5, 64 x 4 30.6).
+void tile_shape(const Layout& L, int& tx, int& ty) {
+    auto fits = [](int w, int h) {
+        return w >= 1 && h >= 1 && w * h <= kTileNodes && (w + 2) * (h + 2) <= kTileCells &&
+               2 * (w + 2) + 2 * h <= kTileNodes;
+    };
+    if (tx && fits(tx, ty)) return;
+    tx = kTileX;
+    ty = kTileY;
+    if (L.whole && L.NX % kTileX == 0) return;
+    const double word = double(slot_bytes(L.prec, 1));
+    double best = 0;
+    for (int nx = 1; nx <= L.NX; ++nx) {
+        const int w = (L.NX + nx - 1) / nx;
+        const bool fit = L.whole && L.NX % w == 0 && int(w * word) % 128 == 0;
+        if (nx > 1 && w < 32) break;
+        if (nx > 1 && w < 48 && !fit) continue;
+        int h = std::min(L.NY, kTileNodes / w);
+        while (h > 0 && !fits(w, h)) --h;
+        if (h < 1) continue;
+        const int ny = (L.NY + h - 1) / h;
+        h = (L.NY + ny - 1) / ny;
+        auto lines = [&](int n) { return (n * word + 128 - word) / 128; };
+        const double cost = double(nx) * ny * (1.0 + (h * (fit ? w * word / 128 : lines(w)) + lines(w + 2) + h) / 16.0);
+        if (best == 0 || cost < best) {
+            best = cost;
+            tx = w;
+            ty = h;
+        }
+    }
+}
+
+// work-groups for tiles of tx x ty nodes
+Tiles make_tiles(const Layout& L, int tx, int ty) {
+    Tiles t{};
+    t.tx = tx;
+    t.ty = ty;
+    t.gx = (L.NX + tx - 1) / tx;
+    t.gy = (L.NY + ty - 1) / ty;
+    const long long cols = std::max(1LL, (long long)t.gx * t.gy);
+    long long nchunks;
+    if (L.dim == 2) {
+        // rows of TX nodes: about 2048 work-groups (8 per compute unit); a 512^2 box then
+        // takes one or two rows per group, the fastest on one MI355X (measured)
+        nchunks = 2048 / cols;
+    } else {
+        // 3D columns: measured on one MI355X (256 compute units), the step is fastest when
+        // all of its work-groups are resident at once, with two per compute unit for
+        // FP32 / FP64 storage (HBM-bound: 15.2 GLUPS at 256^3 against 14.5 with 2048
+        // groups) and three for 16-bit storage (instruction-bound: 21.4 against 20.5);
+        // when the columns alone exceed that, with 64-plane chunks (512^3 BF16: 20.9
+        // GLUPS against 20.0 with 256-plane chunks).  Equal chunks: zc divides nz evenly
+        // when it can.  The layout depends only on the configuration, never on the device.
+        constexpr long long kCUs = 256;
+        const long long per_cu = (L.prec == LBM_FP32 || L.prec == LBM_FP64) ? 2 : 3;
+        nchunks = cols <= per_cu * kCUs ? (per_cu * kCUs) / cols : (L.NZ + 63) / 64;
+    }
+    nchunks = std::max(1LL, std::min<long long>(L.NZ, nchunks));
+    t.zc = int((L.NZ + nchunks - 1) / nchunks);
+    if (const char* e = std::getenv("LBM_ZC")) {
+        const int v = std::atoi(e);
+        if (v > 0) t.zc = std::min(v, L.NZ);
+    }
+    t.gz = (L.NZ + t.zc - 1) / t.zc;
+    return t;
+}
 
 int check_config(const lbm_config* c, Layout* L) {
     if (!c) return fail(LBM_EINVAL, "config is NULL");
@@ -218,45 +300,33 @@ int check_config(const lbm_config* c, Layout* L) {
         L->ks = L->dim == 2 ? kernels_paper_2d(L->qf, L->prec) : kernels_paper_3d(L->qf, L->prec);
         if (!L->ks) return fail(LBM_EUNSUPPORTED, "no kernel for the D2Q9 / D3Q19 scalar lattices at this precision");
     } else {
-        L->ks = L->dim == 2 ? kernels_2d(L->qf, L->prec, want_tx) : kernels_3d(L->qf, L->prec, want_tx, want_ty);
+        L->ks = L->dim == 2 ? kernels_2d(L->qf, L->prec, want_tx) : kernels_3d(L->qf, L->prec);
     }
     if (!L->ks) return fail(LBM_EUNSUPPORTED, "no kernel for this lattice / precision");
-    L->tx = L->ks->tx;
-    L->ty = L->ks->ty;
-    const long long gx = (L->NX + L->tx - 1) / L->tx, gy = (L->NY + L->ty - 1) / L->ty;
-    const long long cols = std::max(1LL, gx * gy);
-    long long nchunks;
+    // rows of whole lines take non-temporal stores
+    L->whole = (long long)L->NX * slot_bytes(L->prec, 1) % 128 == 0;
     if (L->dim == 2) {
-        // rows of TX nodes: about 2048 work-groups (8 per compute unit); a 512^2 box then
-        // takes one or two rows per group, the fastest on one MI355X (measured)
-        nchunks = 2048 / cols;
+        L->line = L->gen = make_tiles(*L, L->ks->nt, 1);
     } else {
-        // 3D columns: measured on one MI355X (256 compute units), the step is fastest when
-        // all of its work-groups are resident at once, with two per compute unit for
-        // FP32 / FP64 storage (HBM-bound: 15.2 GLUPS at 256^3 against 14.5 with 2048
-        // groups) and three for 16-bit storage (instruction-bound: 21.4 against 20.5);
-        // when the columns alone exceed that, with 64-plane chunks (512^3 BF16: 20.9
-        // GLUPS against 20.0 with 256-plane chunks).  Equal chunks: zc divides nz evenly
-        // when it can.  The layout depends only on the configuration, never on the device.
-        constexpr long long kCUs = 256;
-        const long long per_cu = (L->prec == LBM_FP32 || L->prec == LBM_FP64) ? 2 : 3;
-        nchunks = cols <= per_cu * kCUs ? (per_cu * kCUs) / cols : (L->NZ + 63) / 64;
+        L->line = make_tiles(*L, kTileX, kTileY);
+        tile_shape(*L, want_tx, want_ty);
+        L->gen = make_tiles(*L, want_tx, want_ty);
     }
-    nchunks = std::max(1LL, std::min<long long>(L->NZ, nchunks));
-    int zc = int((L->NZ + nchunks - 1) / nchunks);
-    if (const char* e = std::getenv("LBM_ZC")) {
-        const int v = std::atoi(e);
-        if (v > 0) zc = std::min(v, L->NZ);
-    }
-    L->zc = zc;
-    const long long gz = (L->NZ + zc - 1) / zc;
-    L->tiles[0] = int(gx); L->tiles[1] = int(gy); L->tiles[2] = int(gz);
     // Without the phi stencil (no flow, or moments of the scalars alone) a plane needs
     // nothing of the one before: in 3D one plane per work-group, two on large grids, so that
     // the loads of many groups overlap (96^3 FP64 step 67.2 -> 61.2 us, 256^3 FP32 580 ->
     // 550 us against the chunks above; 2D rows measured the same either way)
-    L->zc_flat = L->dim == 2 || L->tuned ? zc : (gx * gy * L->NZ > 8192 ? 2 : 1);
-    L->nparts = gx * gy * gz;
+    L->zc_flat = L->dim == 2 || L->tuned ? 0 : (L->line.gx * L->line.gy * (long long)L->NZ > 8192 ? 2 : 1);
+    // The general kernel where its plain stores or its tiles are worth its registers: rows
+    // that are not whole lines (FP64: if the tiles are fewer, 87 x 123 x 70 with D3Q19 scalars
+    // 276 us a step against 336; otherwise its rows are long enough, 61 x 53 x 250 130
+    // against 135), and whole rows of a width that 64 does not divide, in 3D
+    const bool fewer = L->gen.gx * L->gen.gy * 100LL < L->line.gx * L->line.gy * 94LL;
+    if (L->dim == 2) L->gen_steps = !L->whole;
+    else if (L->whole) L->gen_steps = L->NX % kTileX != 0;
+    else L->gen_steps = L->prec != LBM_FP64 || fewer;
+    L->gen_steps = L->gen_steps || L->tuned;
+    L->nparts = std::max(L->line.groups(), L->gen.groups());
     // aux: kAuxHead doubles of scalars, then per-work-group partials (8 per group
     // of the fused kernel, 9 with a third composition; one per group of the Euler
     // characteristic, <= 1024)
@@ -307,15 +377,25 @@ void set_slots(const lbm_handle* h, KParams& kp, const char* src, char* dst) {
     }
 }
 
-// launch of the fused kernel in one of its modes
-void launch_fused(const lbm_handle* h, int mode, KParams& kp, hipStream_t s) {
+// Launch of the fused kernel in one of its modes; gen: the general kernel (steps).  Returns
+// the work-groups launched (each leaves one entry of partial sums).
+int launch_fused(const lbm_handle* h, int mode, bool gen, KParams& kp, hipStream_t s) {
+    const Layout& L = h->L;
     const bool step = mode == MODE_STEP || mode == MODE_STEP_PHI;
-    const bool flat = mode != MODE_DIAG && (h->L.qf == 0 || mode == MODE_SCALARS);
-    if (flat && !(step && kp.mean_subtract)) {
-        kp.zc = h->L.zc_flat;
-        kp.tiles_z = (kp.nz + kp.zc - 1) / kp.zc;
+    Tiles t = gen ? L.gen : L.line;
+    if (L.zc_flat && mode != MODE_DIAG && (L.qf == 0 || mode == MODE_SCALARS)) {
+        t.zc = L.zc_flat;
+        t.gz = (L.NZ + t.zc - 1) / t.zc;
     }
-    h->ks->fused(mode, dim3(unsigned(kp.tiles_x) * unsigned(kp.tiles_y) * unsigned(kp.tiles_z)), kp, s);
+    kp.tile_x = t.tx;
+    kp.tile_y = t.ty;
+    kp.tile_inv = (65536 + t.tx - 1) / t.tx;
+    kp.zc = t.zc;
+    kp.tiles_x = t.gx;
+    kp.tiles_y = t.gy;
+    kp.tiles_z = t.gz;
+    h->ks->fused(mode, step && gen, unsigned(t.groups()), kp, s);
+    return int(t.groups());
 }
 
 void fill_params(lbm_handle* h) {
@@ -331,8 +411,6 @@ void fill_params(lbm_handle* h) {
         kp.wall_x = c.bc[0] == LBM_WALLS; kp.wall_y = c.bc[1] == LBM_WALLS; kp.wall_z = c.bc[2] == LBM_WALLS;
         kp.gx = c.g[0]; kp.gy = c.g[1]; kp.gz = c.g[2];
     }
-    kp.zc = L.zc;
-    kp.tiles_x = L.tiles[0]; kp.tiles_y = L.tiles[1]; kp.tiles_z = L.tiles[2];
     kp.mean_subtract = c.gravity_mean_subtract ? 1 : 0;
     kp.W = c.W;
     kp.lam = c.lambda;
@@ -642,14 +720,22 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
         }
         return LBM_OK;
     }
-    // walls on x and y: the fix-up kernel; z walls bounce back when the next step pulls
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
+    // 3D with x or y walls: the general kernel bounces back there when it pulls, which saves
+    // the exchange after each step; on large grids of whole lines its plain stores cost more
+    // (128^3 FP32, closed: 191 us a step -> 165; 256^3: 1172 -> 1295)
+    const bool pull_xy = h->L.dim == 3 && nsteps > 1 && (walls[0] || walls[1]) &&
+                         (h->L.gen_steps || h->L.nodes < (1 << 22));
+    const bool gen = h->L.gen_steps || pull_xy;
     for (int64_t i = 0; i < nsteps; ++i) {
-        launch_fused(h, MODE_STEP, kp[h->cur], s);
+        const int groups = launch_fused(h, MODE_STEP, gen, kp[h->cur], s);
+        // only the state that the call leaves is exchanged
+        const bool raw = pull_xy && i + 1 < nsteps;
         for (int a = 0; a < 2; ++a)
-            if (walls[a]) h->ks->walls(kp[h->cur], a, s);
+            if (walls[a] && !raw) h->ks->walls(kp[h->cur], a, s);
+        kp[1 - h->cur].raw_xy = raw;
         if (h->cfg.gravity_mean_subtract)
-            launch_finalize(h->aux + kAuxHead, int(h->L.nparts), 1, -1, 1.0 / double(h->L.nodes), h->aux, s);
+            launch_finalize(h->aux + kAuxHead, groups, 1, -1, 1.0 / double(h->L.nodes), h->aux, s);
         if (int r = launched("step kernel")) return r;
         h->cur ^= 1;
         h->steps += 1;
@@ -686,7 +772,7 @@ int lbm_moments(lbm_handle* h, uint32_t mask, void* const* out, int32_t out_dtyp
     kp.mout_f32 = out_dtype == LBM_OUT_F32;
     if (mask) {
         const uint32_t flow = LBM_M_P | LBM_M_UX | LBM_M_UY | LBM_M_UZ;
-        launch_fused(h, mask & flow ? MODE_MOMENTS : MODE_SCALARS, kp, s);
+        launch_fused(h, mask & flow ? MODE_MOMENTS : MODE_SCALARS, false, kp, s);
         if (int r = launched("moments kernel")) return r;
     }
     return LBM_OK;
@@ -723,9 +809,9 @@ int lbm_diagnostics(lbm_handle* h, double* host_out, void* stream) {
     KParams kp = h->base;
     set_slots(h, kp, h->copy[h->cur], nullptr);
     kp.mask_out = h->mask;
-    launch_fused(h, MODE_DIAG, kp, s);
+    const int groups = launch_fused(h, MODE_DIAG, false, kp, s);
     // 8 reductions (9 with a third composition: sum c^C goes to LBM_D_SUM_CC)
-    launch_finalize(h->aux + kAuxHead, int(h->L.nparts), h->L.nc == 3 ? 9 : 8, 4, 1.0, h->aux + 8, s);
+    launch_finalize(h->aux + kAuxHead, groups, h->L.nc == 3 ? 9 : 8, 4, 1.0, h->aux + 8, s);
     // droplet count: Euler characteristic of the cells with phi >= 1/2, over the
     // axes of the run (2D runs: user x and y; 3D runs with nz = 1 count as 2D)
     const EulerGeom g = euler_geometry(h);
@@ -836,12 +922,12 @@ int lbm_step_external(lbm_handle* h, const void* src, void* dst, void* phi_src, 
     kp.phi_ref = ref_in;
     // the buffered <phi> is recomputed with the mean subtraction, else carried over
     kp.ref_copy = h->cfg.gravity_mean_subtract ? nullptr : ref_out;
-    launch_fused(h, phi_src ? MODE_STEP_PHI : MODE_STEP, kp, s);
+    const int groups = launch_fused(h, phi_src ? MODE_STEP_PHI : MODE_STEP, h->L.gen_steps || (phi_src && !h->ks->adj_step), kp, s);
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
     for (int a = 0; a < 2; ++a)
         if (walls[a]) h->ks->walls(kp, a, s);
     if (h->cfg.gravity_mean_subtract)
-        launch_finalize(h->aux + kAuxHead, int(h->L.nparts), 1, -1, 1.0 / double(h->L.nodes), ref_out, s);
+        launch_finalize(h->aux + kAuxHead, groups, 1, -1, 1.0 / double(h->L.nodes), ref_out, s);
     return launched("step_external kernels");
 }
 
@@ -854,7 +940,7 @@ int lbm_phase_field(lbm_handle* h, const void* state, void* phi, void* stream) {
     for (int i = 0; i < kNumMom; ++i) kp.mout[i] = nullptr;
     kp.mout[0] = phi;
     kp.mout_f32 = h->L.prec == LBM_FP64 ? 0 : 1;
-    launch_fused(h, MODE_SCALARS, kp, static_cast<hipStream_t>(stream));
+    launch_fused(h, MODE_SCALARS, false, kp, static_cast<hipStream_t>(stream));
     return launched("phase-field kernel");
 }
 

@@ -9,8 +9,8 @@ const KernelSet* mrt2d_q9(int fluid, int prec);
 
 const KernelSet* kernels_mrt_2d(int scalar, int fluid, int prec) {
     if (scalar == 5) {
-        if (fluid == 0) return family_all_prec_noadj<D2Q5K, NoLattice, 256, 1, COLL_MRT>(prec);
-        if (fluid == 9) return family_all_prec_noadj<D2Q5K, D2Q9K, 256, 1, COLL_MRT>(prec);
+        if (fluid == 0) return family_all_prec_noadj<D2Q5K, NoLattice, 256, COLL_MRT>(prec);
+        if (fluid == 9) return family_all_prec_noadj<D2Q5K, D2Q9K, 256, COLL_MRT>(prec);
     } else if (scalar == 9) {
         return mrt2d_q9(fluid, prec);
     }

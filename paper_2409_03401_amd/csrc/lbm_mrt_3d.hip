@@ -11,8 +11,8 @@ const KernelSet* mrt3d_q19_flow_16(int prec);
 
 const KernelSet* kernels_mrt_3d(int scalar, int fluid, int prec) {
     if (scalar == 7) {
-        if (fluid == 0) return family_all_prec_noadj<D3Q7K, NoLattice, 64, 4, COLL_MRT>(prec);
-        if (fluid == 19) return family_all_prec_noadj<D3Q7K, D3Q19K, 64, 4, COLL_MRT>(prec);
+        if (fluid == 0) return family_all_prec_noadj<D3Q7K, NoLattice, kTileNodes, COLL_MRT>(prec);
+        if (fluid == 19) return family_all_prec_noadj<D3Q7K, D3Q19K, kTileNodes, COLL_MRT>(prec);
     } else if (scalar == 19) {
         if (fluid == 0) return mrt3d_q19(fluid, prec);
         if (fluid == 19) return (prec == P64 || prec == P32) ? mrt3d_q19_flow_fp(prec) : mrt3d_q19_flow_16(prec);

@@ -3,6 +3,6 @@
 
 namespace lbm {
 
-const KernelSet* mrt3d_q19(int, int prec) { return family_all_prec_noadj<D3Q19K, NoLattice, 64, 4, COLL_MRT>(prec); }
+const KernelSet* mrt3d_q19(int, int prec) { return family_all_prec_noadj<D3Q19K, NoLattice, kTileNodes, COLL_MRT>(prec); }
 
 }  // namespace lbm

@@ -5,8 +5,8 @@
 namespace lbm {
 
 const KernelSet* mrt3d_q19_flow_16(int prec) {
-    if (prec == P16) return family_one_prec<D3Q19K, D3Q19K, 64, 4, COLL_MRT, P16>();
-    if (prec == PB16) return family_one_prec<D3Q19K, D3Q19K, 64, 4, COLL_MRT, PB16>();
+    if (prec == P16) return family_one_prec<D3Q19K, D3Q19K, kTileNodes, COLL_MRT, P16>();
+    if (prec == PB16) return family_one_prec<D3Q19K, D3Q19K, kTileNodes, COLL_MRT, PB16>();
     return nullptr;
 }
 

@@ -6,8 +6,8 @@
 namespace lbm {
 
 const KernelSet* kernels_nc3_2d(int fluid, int prec) {
-    if (fluid == 0) return family_nc3<D2Q5K, NoLattice, 256, 1>(prec);
-    if (fluid == 9) return family_nc3<D2Q5K, D2Q9K, 256, 1>(prec);
+    if (fluid == 0) return family_nc3<D2Q5K, NoLattice, 256>(prec);
+    if (fluid == 9) return family_nc3<D2Q5K, D2Q9K, 256>(prec);
     return nullptr;
 }
 

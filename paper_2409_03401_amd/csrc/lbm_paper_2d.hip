@@ -8,8 +8,8 @@
 namespace lbm {
 
 const KernelSet* kernels_paper_2d(int fluid, int prec) {
-    if (fluid == 0) return family_for_prec<D2Q9K, NoLattice, 256, 1>(prec);
-    if (fluid == 9) return family_for_prec<D2Q9K, D2Q9K, 256, 1>(prec);
+    if (fluid == 0) return family_for_prec<D2Q9K, NoLattice, 256>(prec);
+    if (fluid == 9) return family_for_prec<D2Q9K, D2Q9K, 256>(prec);
     return nullptr;
 }
 

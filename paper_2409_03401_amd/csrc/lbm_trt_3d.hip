@@ -6,11 +6,11 @@ namespace lbm {
 
 const KernelSet* kernels_trt_3d(int scalar, int fluid, int prec) {
     if (scalar == 7) {
-        if (fluid == 0) return family_all_prec_noadj<D3Q7K, NoLattice, 64, 4, COLL_TRT>(prec);
-        if (fluid == 19) return family_all_prec_noadj<D3Q7K, D3Q19K, 64, 4, COLL_TRT>(prec);
+        if (fluid == 0) return family_all_prec_noadj<D3Q7K, NoLattice, kTileNodes, COLL_TRT>(prec);
+        if (fluid == 19) return family_all_prec_noadj<D3Q7K, D3Q19K, kTileNodes, COLL_TRT>(prec);
     } else if (scalar == 19) {
-        if (fluid == 0) return family_all_prec_noadj<D3Q19K, NoLattice, 64, 4, COLL_TRT>(prec);
-        if (fluid == 19) return family_all_prec_noadj<D3Q19K, D3Q19K, 64, 4, COLL_TRT>(prec);
+        if (fluid == 0) return family_all_prec_noadj<D3Q19K, NoLattice, kTileNodes, COLL_TRT>(prec);
+        if (fluid == 19) return family_all_prec_noadj<D3Q19K, D3Q19K, kTileNodes, COLL_TRT>(prec);
     }
     return nullptr;
 }

@@ -6,11 +6,11 @@ namespace lbm {
 
 const KernelSet* kernels_vd_3d(int scalar, bool trt, int prec) {
     if (scalar == 7)
-        return trt ? family_all_prec_noadj<D3Q7K, D3Q19K, 64, 4, COLL_VD | COLL_TRT>(prec)
-                   : family_all_prec_noadj<D3Q7K, D3Q19K, 64, 4, COLL_VD>(prec);
+        return trt ? family_all_prec_noadj<D3Q7K, D3Q19K, kTileNodes, COLL_VD | COLL_TRT>(prec)
+                   : family_all_prec_noadj<D3Q7K, D3Q19K, kTileNodes, COLL_VD>(prec);
     if (scalar == 19)
-        return trt ? family_all_prec_noadj<D3Q19K, D3Q19K, 64, 4, COLL_VD | COLL_TRT>(prec)
-                   : family_all_prec_noadj<D3Q19K, D3Q19K, 64, 4, COLL_VD>(prec);
+        return trt ? family_all_prec_noadj<D3Q19K, D3Q19K, kTileNodes, COLL_VD | COLL_TRT>(prec)
+                   : family_all_prec_noadj<D3Q19K, D3Q19K, kTileNodes, COLL_VD>(prec);
     return nullptr;
 }
 

@@ -9,6 +9,12 @@
 
 namespace lbm {
 
+// threads of a 3D work-group, and the largest tile with its ring of one node (the host
+// keeps tile_x tile_y <= kTileNodes, (tile_x + 2) (tile_y + 2) <= kTileCells and
+// 2 (tile_x + 2) + 2 tile_y <= kTileNodes: one ring node per thread)
+constexpr int kTileNodes = 256, kTileCells = 464;
+// the tile of grids whose rows are whole lines
+constexpr int kTileX = 64, kTileY = 4;
 // D3Q19 fluid + 3 x D3Q19 scalars (the paper's lattices), or D3Q19 + 4 x D3Q7 (a third
 // composition on the reduced lattice)
 constexpr int kMaxSlots = 19 + 3 * 19;
@@ -48,6 +54,9 @@ struct KParams {
     int wall_x, wall_y, wall_z;  // 1: half-way bounce-back walls on that axis
     int zc;                      // planes marched per work-group
     int tiles_x, tiles_y, tiles_z;  // work-group tiles per axis (tiles_z = z chunks)
+    int tile_x, tile_y;          // nodes of a tile (3D; 2D: a row segment of the work-group's size)
+    int tile_inv;                // ceil(65536 / tile_x): (t * tile_inv) >> 16 = t / tile_x for t < 256
+    int raw_xy;                  // the source copy holds raw populations at the x and y walls
     int mean_subtract;           // buoyancy uses phi - phi_ref
     // model (Section 2), lattice units
     double W, lam, mphi_w2;      // mphi_w2 = M_phi / W^2 = 1 / tau_phi
