@@ -116,6 +116,7 @@ constexpr int lbm_waves() {
     constexpr bool s16 = PREC == P16 || PREC == PB16;
     constexpr bool coll = (COLL & COLL_GK) == 0 && ((COLL & COLL_MRT) == 0 || PREC == PB16);
     if constexpr (s16 && SL::Q == 19 && coll) return 2;
+    if constexpr (PREC == P32 && SL::Q == 19 && QF > 0) return 2;
     if constexpr (s16 && SL::Q == 7 && (COLL & COLL_GK) != 0) return 3;
     if constexpr (PREC == PB16 && SL::Q == 7 && NC == 3) return 3;
     if constexpr (s16 && SL::DIM == 2 && QF > 0) {
@@ -156,13 +157,22 @@ k_lbm(const KParams P) {
     static_assert(SLOTS::N <= kMaxSlots, "slot table too small for this lattice family");
     constexpr bool VD = NODE::VD;
     constexpr bool GK = NODE::GK;
-    // the private LDS ring of scalar populations, unless it would not leave room for a
-    // second work-group per compute unit (the paper's D3Q19 scalar lattice in FP32 / FP64,
-    // and with the general-curvature collision or MRT with FP16).  The other D3Q19
-    // kernels with 16-bit storage take the packed ring (30 words per node and plane,
-    // 61 KB) and two waves per SIMD (lbm_waves)
-    constexpr bool LDS_POPS = LBM_LDS_POPS && (lbm_waves<SL, PREC, COLL, NC, FL::Q>() == 2 ||
-                                               2 * (1 + NC) * QS * NT * sizeof(C) <= 96 * 1024);
+    // the private LDS ring of scalar populations: two planes where they leave room for a
+    // second work-group per compute unit.  One plane, exchanged in place (INPLACE: the next
+    // plane's populations go in as the current plane's come out), for FP64 on D3Q7 and FP32
+    // on D3Q19 scalars: half the LDS, two work-groups per compute unit instead of one.  The
+    // D3Q19 kernels with 16-bit storage take the packed ring (30 words per node and plane,
+    // 61 KB) and two waves per SIMD (lbm_waves).  FP64 on D3Q19 keeps the next plane in
+    // registers (117 KB a plane)
+    constexpr int PLANE = (1 + NC) * QS * NT * int(sizeof(C));
+    constexpr bool S16 = PREC == P16 || PREC == PB16;
+    // wall planes replace their bounced populations after the common loads instead of taking a
+    // copy of the whole fill: in the general kernel, and where the copy crowds the registers
+    // (128^3 D3Q19 scalars BF16 210 us a step against 230)
+    constexpr bool REPL = GEN || (S16 && QS == 19);
+    constexpr bool INPLACE = HAS_Y && STENCIL && !S16 && 2 * PLANE > 64 * 1024 && PLANE <= 64 * 1024;
+    constexpr bool LDS_POPS = LBM_LDS_POPS && (INPLACE || lbm_waves<SL, PREC, COLL, NC, FL::Q>() == 2 ||
+                                               2 * PLANE <= 96 * 1024);
     static_assert((QS - 1) % 2 == 0, "moving directions come in opposite pairs");
 
     __shared__ C sphi[NSLOT][CELLS];
@@ -177,7 +187,7 @@ k_lbm(const KParams P) {
     constexpr int NPAIR = (QS - 1) / 2;
     constexpr int NWORD = PACKED ? (1 + NC) * (1 + NPAIR) : (1 + NC) * QS;
     using W = typename std::conditional<PACKED, unsigned, C>::type;
-    __shared__ W spop[(STENCIL && LDS_POPS) ? 2 : 1][(STENCIL && LDS_POPS) ? NWORD : 1][(STENCIL && LDS_POPS) ? NT : 1];
+    __shared__ W spop[(STENCIL && LDS_POPS && !INPLACE) ? 2 : 1][(STENCIL && LDS_POPS) ? NWORD : 1][(STENCIL && LDS_POPS) ? NT : 1];
 
     const int tid = threadIdx.x;
     const int tw = HAS_Y ? (GEN ? P.tile_x : kTileX) : NT, th = HAS_Y ? (GEN ? P.tile_y : kTileY) : 1;
@@ -257,7 +267,7 @@ k_lbm(const KParams P) {
         return ld_at<PREC, SLOTS::rest(S), ONCE>(src(s_), idx, wref_dec(s_, k_, lat_), P.finv[SLOTS::field(S)]);
     };
     // scalar populations arriving at node idx (pull from idx - e_k; the node's own opposite
-    // population where that crosses a z wall: zlo / zhi, wave-uniform).  GEN: bounce_pops
+    // population where that crosses a z wall: zlo / zhi, wave-uniform).  REPL: bounce_pops
     // replaces those that bounce back at any wall (a branch that only planes and tiles at a
     // wall take, its loads in the same batch)
     // The scalar populations of a node in their stored form (RAW: 16-bit storage keeps
@@ -283,7 +293,7 @@ k_lbm(const KParams P) {
     auto load_pops = [&](unsigned idx, const Nbr& nb, bool zlo, bool zhi, RW (&raw)[NSC]) __attribute__((always_inline)) {
         static_for<0, QS>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value, o = SL::opp(k);
-            if (!GEN && zbounce<SL::ez(k)>(zlo, zhi)) pops_at(kc, IC<o>{}, idx, raw);
+            if (!REPL && zbounce<SL::ez(k)>(zlo, zhi)) pops_at(kc, IC<o>{}, idx, raw);
             else pops_at(kc, kc, unsigned(int(idx) + pull_offset<SL::ex(k), SL::ey(k), SL::ez(k)>(nb)), raw);
         });
     };
@@ -315,7 +325,7 @@ k_lbm(const KParams P) {
                             __attribute__((always_inline)) {
         RW raw[NSC];
         load_pops(idx, nb, zlo, zhi, raw);
-        if (GEN && (zlo || zhi || edge)) bounce_pops(idx, zlo, zhi, x, y, raw);
+        if (REPL && (zlo || zhi || edge)) bounce_pops(idx, zlo, zhi, x, y, raw);
         decode_pops(raw, gg, aa, bb, qq);
         NODE::pop_sums(gg, aa, bb, qq, phis, cA, cB, cC);
     };
@@ -374,7 +384,7 @@ k_lbm(const KParams P) {
                            double& cB, double& cC) __attribute__((always_inline)) {
         RW raw[NSC];
         load_pops(idx, nb, zlo, zhi, raw);
-        if (GEN && (zlo || zhi)) bounce_pops(idx, zlo, zhi, x, y, raw);
+        if (REPL && (zlo || zhi)) bounce_pops(idx, zlo, zhi, x, y, raw);
         finish_packed(raw, pbuf, phis, cA, cB, cC);
     };
 
@@ -404,7 +414,7 @@ k_lbm(const KParams P) {
         const unsigned oi = unsigned((zm * P.ny + oy) * P.nx + ox), ri = unsigned((zm * P.ny + ry) * P.nx + rx);
         load_pops(oi, neighbours(ox, oy, zm, P), zlo, zhi, own);
         load_pops(ri, neighbours(rx, ry, zm, P), zlo, zhi, ring);
-        if (GEN && (zlo || zhi || edge)) {
+        if (REPL && (zlo || zhi || edge)) {
             bounce_pops(oi, zlo, zhi, ox, oy, own);
             bounce_pops(ri, zlo, zhi, rx, ry, ring);
         }
@@ -416,6 +426,17 @@ k_lbm(const KParams P) {
         } else if constexpr (LDS_POPS) {
             C gg[QS], aa[QS], bb[QS], qq[QC];
             decode_pops(own, gg, aa, bb, qq);
+            if constexpr (INPLACE) {
+                // the current plane's populations come out (of the prologue's fills nothing does)
+#pragma unroll
+                for (int k = 0; k < QS; ++k) {
+                    cg[k] = spop[0][k][tid];
+                    ca[k] = spop[0][QS + k][tid];
+                    cb[k] = spop[0][2 * QS + k][tid];
+                    if constexpr (NC3) cq[k] = spop[0][3 * QS + k][tid];
+                }
+                pbuf = 0;
+            }
 #pragma unroll
             for (int k = 0; k < QS; ++k) {
                 spop[pbuf][k][tid] = gg[k];
@@ -494,9 +515,9 @@ k_lbm(const KParams P) {
                           __attribute__((always_inline)) {
         const int zm = map_coord(zz, P.nz, P.wall_z);
         const bool zlo = P.wall_z && zm == 0, zhi = P.wall_z && zm == P.nz - 1;
-        // not GEN: a z wall plane is a separate, uniform branch, and the interior planes keep
+        // not REPL: a z wall plane is a separate, uniform branch, and the interior planes keep
         // the plain loads
-        if (GEN || zlo || zhi) fill_body(zm, zlo, zhi, slot, pbuf, ps, cA, cB, cC);
+        if (REPL || zlo || zhi) fill_body(zm, zlo, zhi, slot, pbuf, ps, cA, cB, cC);
         else fill_body(zm, false, false, slot, pbuf, ps, cA, cB, cC);
     };
 
@@ -528,7 +549,7 @@ k_lbm(const KParams P) {
                 field(IC<B0>{}, IC<2 * (1 + NPAIR)>{}, cb);
                 if constexpr (NC3) field(IC<HC0>{}, IC<3 * (1 + NPAIR)>{}, cq);
             }
-        } else if constexpr (LDS_POPS && STENCIL) {
+        } else if constexpr (LDS_POPS && STENCIL && !INPLACE) {
             if (active) {
                 const int pb = (zz - z0) & 1;
 #pragma unroll
@@ -588,7 +609,7 @@ k_lbm(const KParams P) {
         auto load_f_body = [&](bool zlo, bool zhi) __attribute__((always_inline)) {
             static_for<0, QF>([&](auto kc) __attribute__((always_inline)) {
                 constexpr int k = decltype(kc)::value;
-                if (!GEN && zbounce<FL::ez(k)>(zlo, zhi)) one_f(kc, IC<FL::opp(k)>{}, idx);
+                if (!REPL && zbounce<FL::ez(k)>(zlo, zhi)) one_f(kc, IC<FL::opp(k)>{}, idx);
                 else one_f(kc, kc, unsigned(int(idx) + pull_offset<FL::ex(k), FL::ey(k), FL::ez(k)>(nbr)));
             });
         };
@@ -631,9 +652,9 @@ k_lbm(const KParams P) {
                     load_f_sel();  // every lane loads (lanes outside the domain: in-range stand-ins)
                     if (GEN && edge && active) bounce_f(zlo, zhi);
                 } else if (active) {
-                    if (GEN || zlo || zhi) load_f_body(zlo, zhi);
+                    if (REPL || zlo || zhi) load_f_body(zlo, zhi);
                     else load_f_body(false, false);
-                    if (GEN && (zlo || zhi || edge)) bounce_f(zlo, zhi);
+                    if (REPL && (zlo || zhi || edge)) bounce_f(zlo, zhi);
                 }
             }
         };
@@ -650,7 +671,7 @@ k_lbm(const KParams P) {
         } else {
             if (active) {
                 const bool zlo = P.wall_z && z == 0, zhi = P.wall_z && z == P.nz - 1;
-                if (GEN || zlo || zhi) load_scalars(idx, nbr, zlo, zhi, cg, ca, cb, cq, c_ps, c_cA, c_cB, c_cC);
+                if (REPL || zlo || zhi) load_scalars(idx, nbr, zlo, zhi, cg, ca, cb, cq, c_ps, c_cA, c_cB, c_cC);
                 else load_scalars(idx, nbr, false, false, cg, ca, cb, cq, c_ps, c_cA, c_cB, c_cC);
             }
         }
