@@ -3,6 +3,8 @@
 // storage precisions.
 #pragma once
 
+#include <algorithm>
+
 #include "block2d.hpp"
 #include "dispatch.hpp"
 #include "kernels.hpp"
@@ -77,10 +79,12 @@ struct Family {
                                kp, nodes, dL_dphi);
     }
     static void adj_gather(const KParams& kp, long long nodes, int mode, double* grad_phi0, hipStream_t s) {
-        const dim3 grid(unsigned((nodes + 255) / 256));
         if constexpr (kAdj) {
-            if (mode == 0) hipLaunchKernelGGL((k_adj_gather<SL, FL, 0>), grid, dim3(256), 0, s, kp, nodes, grad_phi0);
-            else hipLaunchKernelGGL((k_adj_gather<SL, FL, 1>), grid, dim3(256), 0, s, kp, nodes, grad_phi0);
+            using T = GatherTile<SL::DIM>;
+            const long long tiles = ((kp.nx + T::X - 1LL) / T::X) * ((kp.ny + T::Y - 1LL) / T::Y) * ((kp.nz + T::Z - 1LL) / T::Z);
+            const dim3 grid(unsigned(std::min(tiles, (nodes + 255) / 256)));
+            if (mode == 0) hipLaunchKernelGGL((k_adj_gather<SL, FL, 0>), grid, dim3(256), 0, s, kp, int(tiles), grad_phi0);
+            else hipLaunchKernelGGL((k_adj_gather<SL, FL, 1>), grid, dim3(256), 0, s, kp, int(tiles), grad_phi0);
         }
     }
     static void adj_init_local(const KParams& kp, long long nodes, const double* phi0, const double* muA0,
