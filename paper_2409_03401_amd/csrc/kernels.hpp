@@ -1418,6 +1418,18 @@ __global__ void __launch_bounds__(256) k_adj_copy(const KParams P, long long nod
     }
 }
 
+// zero the bytes after each slot of the copies at P.src_slot and P.dst_slot (used_m / used_r
+// bytes of a moving / rest slot are populations)
+template <int NT = 256>
+__global__ void __launch_bounds__(NT) k_zero_padding(const KParams P, int qf, int qs, unsigned long long used_m,
+                                                     unsigned long long used_r) {
+    const int s = blockIdx.x;
+    const bool rest = (s < qf ? s : (s - qf) % qs) == 0;
+    char* slot = blockIdx.y ? P.dst_slot[s] : const_cast<char*>(P.src_slot[s]);
+    const unsigned long long at = (rest ? used_r : used_m) + threadIdx.x;
+    if (at < (rest ? P.stride_r : P.stride_m)) slot[at] = 0;
+}
+
 // zero n doubles
 template <int NT = 256>
 __global__ void __launch_bounds__(NT) k_zero_f64(double* p, long long n) {
@@ -1444,6 +1456,8 @@ __global__ void __launch_bounds__(256) k_finalize(const double* __restrict__ par
     double acc[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) acc[i] = 0.0;
+    // unrolled so that the loads of several rounds are in flight (8192 entries: 15 -> 5 us)
+#pragma unroll 8
     for (int p = threadIdx.x; p < nparts; p += 256) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -1479,14 +1493,15 @@ __global__ void __launch_bounds__(256) k_finalize(const double* __restrict__ par
 template <int D>
 __global__ void __launch_bounds__(256) k_euler(const unsigned char* __restrict__ mask, const EulerGeom G,
                                                double* __restrict__ partials) {
+    // 32-bit indices: a grid has fewer than 2^31 nodes and anchors
     int acc = 0;
-    const long long step = (long long)gridDim.x * 256;
-    for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < G.nanchors; t += step) {
+    const unsigned step = gridDim.x * 256u, n = unsigned(G.nanchors);
+    for (unsigned t = blockIdx.x * 256u + threadIdx.x; t < n; t += step) {
         int j[D];
-        long long r = t;
+        unsigned r = t;
 #pragma unroll
         for (int a = 0; a < D; ++a) {
-            const long long m = G.n[a] + G.wall[a];
+            const unsigned m = unsigned(G.n[a] + G.wall[a]);
             j[a] = int(r % m);
             r /= m;
         }
@@ -1494,7 +1509,7 @@ __global__ void __launch_bounds__(256) k_euler(const unsigned char* __restrict__
         unsigned bits = 0;
 #pragma unroll
         for (int o = 0; o < (1 << D); ++o) {
-            long long off = 0;
+            unsigned off = 0;
             bool in = true;
 #pragma unroll
             for (int a = 0; a < D; ++a) {
@@ -1506,9 +1521,9 @@ __global__ void __launch_bounds__(256) k_euler(const unsigned char* __restrict__
                     if (G.wall[a]) in = false;
                     else c -= G.n[a];
                 }
-                off += (long long)c * G.stride[a];
+                off += in ? unsigned(c) * unsigned(G.stride[a]) : 0u;
             }
-            if (in && mask[off]) bits |= 1u << o;
+            bits |= (unsigned(in) & unsigned(mask[off] != 0)) << o;  // no branch: the loads go out together
         }
 #pragma unroll
         for (int S = 0; S < (1 << D); ++S) {

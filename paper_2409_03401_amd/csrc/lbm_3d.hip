@@ -41,4 +41,9 @@ void launch_zero(double* p, long long n, hipStream_t s) {
     if (n > 0) hipLaunchKernelGGL((k_zero_f64<256>), dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, p, n);
 }
 
+void launch_zero_padding(const KParams& kp, int qf, int qs, int nslots, unsigned long long used_m,
+                         unsigned long long used_r, hipStream_t s) {
+    hipLaunchKernelGGL((k_zero_padding<256>), dim3(unsigned(nslots), 2), dim3(256), 0, s, kp, qf, qs, used_m, used_r);
+}
+
 }  // namespace lbm

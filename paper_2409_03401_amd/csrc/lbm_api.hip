@@ -318,14 +318,9 @@ int check_config(const lbm_config* c, Layout* L) {
     // 550 us against the chunks above; 2D rows measured the same either way)
     L->zc_flat = L->dim == 2 || L->tuned ? 0 : (L->line.gx * L->line.gy * (long long)L->NZ > 8192 ? 2 : 1);
     // The general kernel where its plain stores or its tiles are worth its registers: rows
-    // that are not whole lines (FP64: if the tiles are fewer, 87 x 123 x 70 with D3Q19 scalars
-    // 276 us a step against 336; otherwise its rows are long enough, 61 x 53 x 250 130
-    // against 135), and whole rows of a width that 64 does not divide, in 3D
-    const bool fewer = L->gen.gx * L->gen.gy * 100LL < L->line.gx * L->line.gy * 94LL;
-    if (L->dim == 2) L->gen_steps = !L->whole;
-    else if (L->whole) L->gen_steps = L->NX % kTileX != 0;
-    else L->gen_steps = L->prec != LBM_FP64 || fewer;
-    L->gen_steps = L->gen_steps || L->tuned;
+    // that are not whole lines (87 x 123 x 70 FP64, D3Q19 scalars 276 us a step against 338),
+    // and whole rows of a width that 64 does not divide, in 3D
+    L->gen_steps = !L->whole || (L->dim == 3 && L->NX % kTileX != 0) || L->tuned;
     L->nparts = std::max(L->line.groups(), L->gen.groups());
     // aux: kAuxHead doubles of scalars, then per-work-group partials (8 per group
     // of the fused kernel, 9 with a third composition; one per group of the Euler
@@ -571,9 +566,15 @@ int init_impl(const lbm_config* cfg, void* state, size_t state_bytes, const doub
     }
     if (hipMemsetAsync(h->aux, 0, kAuxHead * sizeof(double), s) != hipSuccess)
         return bail(fail(LBM_EHIP, "hipMemsetAsync of the aux area failed"));
-    // both population copies start zeroed: the padding after each slot is then zero for
-    // good (no kernel writes it), and so are the padding bytes of every checkpoint
-    launch_zero(reinterpret_cast<double*>(h->copy[0]), (long long)(2 * L.copy_bytes / sizeof(double)), s);
+    // the padding after each slot of both copies is zero for good (no kernel writes it), and
+    // so are the padding bytes of every checkpoint; every population is written before it is
+    // read (256^3 FP32: 5.4 GB of zeros, 0.8 ms, half of the initialisation, for nothing)
+    {
+        KParams kz = h->base;
+        set_slots(h, kz, h->copy[0], h->copy[1]);
+        launch_zero_padding(kz, L.qf, L.qs, L.nslots, (unsigned long long)L.nodes * slot_bytes(L.prec, 1),
+                            (unsigned long long)L.nodes * slot_bytes(L.prec, 0), s);
+    }
     if (cfg->gravity_mean_subtract) {
         // <phi_0> for the buoyancy reference of the first step
         const int nb = int(std::min<long long>(1024, (L.nodes + 255) / 256));

@@ -194,21 +194,21 @@ __device__ __forceinline__ float enc_d(float v, float wref, float scale) {
     else return v - wref;
 }
 
-// encode and store one population; populations written by a step are read again
-// only in the next step, so they stream past the caches (non-temporal stores)
+// encode and store one population (initialisation and population access: plain stores, the
+// shifted rows of a pull layout start inside lines)
 template <int PREC, bool REST>
 __device__ __forceinline__ void st_at(char* slot, unsigned idx, float wref, float scale,
                                       typename Stor<PREC>::C v) {
     if constexpr (PREC == P64) {
-        __builtin_nontemporal_store(v, reinterpret_cast<double*>(slot + idx * 8u));
+        *reinterpret_cast<double*>(slot + idx * 8u) = v;
     } else if constexpr (PREC == P32 || REST) {
-        __builtin_nontemporal_store(float(v), reinterpret_cast<float*>(slot + idx * 4u));
+        *reinterpret_cast<float*>(slot + idx * 4u) = float(v);
     } else {
         const float d = enc_d<PREC>(v, wref, scale);
         unsigned short bits;
         if constexpr (PREC == P16) bits = __half_as_ushort(__float2half_rn(d));
         else bits = __builtin_bit_cast(unsigned short, __bf16(d));  // round to nearest even
-        __builtin_nontemporal_store(bits, reinterpret_cast<unsigned short*>(slot + idx * 2u));
+        *reinterpret_cast<unsigned short*>(slot + idx * 2u) = bits;
     }
 }
 
@@ -233,7 +233,7 @@ __device__ __forceinline__ typename Stor<PREC>::C st_at_r(char* slot, unsigned i
             bits = __builtin_bit_cast(unsigned short, bd);
             back = float(bd);
         }
-        __builtin_nontemporal_store(bits, reinterpret_cast<unsigned short*>(slot + idx * 2u));
+        *reinterpret_cast<unsigned short*>(slot + idx * 2u) = bits;
         return back + wref;
     }
 }
@@ -280,7 +280,7 @@ __device__ __forceinline__ unsigned enc2_dev(float wref, float scale, float va, 
 }
 
 // store the stored form of one population: the 16 bits of a moving population, or the
-// value itself (FP32 / FP64 storage, rest populations).  STREAM: a non-temporal store, for
+// value itself (FP32 / FP64 storage, rest populations), as a step writes it.  STREAM: a non-temporal store, for
 // whole 128-byte lines that nobody reads before the next step (256^3 FP32 1114 us a step
 // against 1200 with plain stores, 512^3 BF16 5660 against 6200).  Rows that start inside a
 // line take plain stores: L2 joins the parts of a line that neighbouring waves and rows
@@ -291,23 +291,6 @@ __device__ __forceinline__ void st_raw(char* slot, unsigned idx, V v) {
     V* p = reinterpret_cast<V*>(slot + idx * unsigned(sizeof(V)));
     if constexpr (STREAM) __builtin_nontemporal_store(v, p);
     else *p = v;
-}
-
-// runtime-slot variants (generic copy kernels)
-template <int PREC>
-__device__ __forceinline__ typename Stor<PREC>::C ld_pop(const void* base, int idx, bool rest,
-                                                         float wref, float inv_scale) {
-    const char* p = static_cast<const char*>(base);
-    if (rest) return ld_at<PREC, true>(p, unsigned(idx), wref, inv_scale);
-    return ld_at<PREC, false>(p, unsigned(idx), wref, inv_scale);
-}
-
-template <int PREC>
-__device__ __forceinline__ void st_pop(void* base, int idx, bool rest, float wref, float scale,
-                                       typename Stor<PREC>::C v) {
-    char* p = static_cast<char*>(base);
-    if (rest) st_at<PREC, true>(p, unsigned(idx), wref, scale, v);
-    else st_at<PREC, false>(p, unsigned(idx), wref, scale, v);
 }
 
 }  // namespace lbm
