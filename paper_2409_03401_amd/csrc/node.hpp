@@ -120,6 +120,17 @@ struct Node {
         if constexpr (PREC == P64) return __builtin_fma(v[2], w[2], __builtin_fma(v[1], w[1], v[0] * w[0]));
         else return v[0] * w[0] + v[1] * w[1] + v[2] * w[2];
     }
+    // e_k . (hs F) with Fh = hs F.  Variable density in 3D: fused by hand as in `flow`
+    template <int ex, int ey, int ez>
+    static __device__ __forceinline__ C edot_scaled(C hs, const C (&F)[3], const C (&Fh)[3]) {
+        if constexpr (VD && SL::DIM == 3 && PREC != P64 && ex * ex + ey * ey + ez * ez == 2) {
+            constexpr int i = ex != 0 ? 0 : 1, j = ez != 0 ? 2 : 1;
+            constexpr int si = i == 0 ? ex : ey, sj = j == 2 ? ez : ey;
+            return __builtin_elementwise_fma(si > 0 ? hs : -hs, F[i], sj > 0 ? Fh[j] : -Fh[j]);
+        } else {
+            return edot<ex, ey, ez>(Fh[0], Fh[1], Fh[2]);
+        }
+    }
     static __device__ __forceinline__ void pin1(C& x) { asm("" : "+v"(x)); }
     template <class... T>
     static __device__ __forceinline__ void pin(T&... x) {
@@ -271,12 +282,15 @@ struct Node {
             const C nuv = sum2(KC(P.nu0, P.f32.nu0), C(1) - phi, KC(P.nu1, P.f32.nu1), phi);
             const C coef = -C(3) * nuv * rcp<C>(C(3) * nuv + C(0.5)) * drho;
             const C px[3] = {pxx, pxy, pxz}, py[3] = {pxy, pyy, pyz}, pz[3] = {pxz, pyz, pzz};
-            C Fm[3] = {coef * dot3(px, grad), coef * dot3(py, grad), coef * dot3(pz, grad)};
-            pin(Fm[0], Fm[1], Fm[2]);
+            const C dots[3] = {dot3(px, grad), dot3(py, grad), dot3(pz, grad)};
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                u[a] = us[a] + C(0.5) * Fm[a] * irho;
-                F[a] += fp * grad[a] + Fm[a];
+                C Fm = coef * dots[a];
+                pin(Fm);
+                u[a] = us[a] + C(0.5) * Fm * irho;
+                // fused by hand, as the compiler does or does not by the order in which it
+                // meets the two products; 16-bit states show the difference
+                F[a] += __builtin_elementwise_fma(coef, dots[a], fp * grad[a]);
             }
         }
         pin(u[0], u[1], u[2], F[0], F[1], F[2], p_h);
@@ -397,7 +411,7 @@ struct Node {
                     constexpr int ex = FL::ex(k), ey = FL::ey(k), ez = FL::ez(k);
                     const C wk = C(FL::w(k));  // w_opp(k) = w_k
                     const C eu = edot<ex, ey, ez>(u[0], u[1], u[2]);
-                    const C eF = edot<ex, ey, ez>(Fh[0], Fh[1], Fh[2]);
+                    const C eF = edot_scaled<ex, ey, ez>(hs, F, Fh);
                     const C e2 = eu * eu;
                     const C q = C(1.5) * e2;
                     const C r = g0 + C(4.5) * e2;
