@@ -106,11 +106,14 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[N], int maxslot, 
 // - 2D with 16-bit storage and flow, kernels of 129-146 registers (three waves): four
 //   waves per SIMD measured at 2048^2 +9-13 % with a third composition, +13-14 % for the
 //   variable-density model on D2Q9 scalars, +14 % for the paper's D2Q9 lattices with
-//   FP16, +8 % for MRT on D2Q5 with BF16.
+//   FP16, +8 % for MRT on D2Q5 with BF16;
+// - the D3Q19 scalar lattices with flow in FP32, whose one-plane LDS ring lets two
+//   work-groups share a compute unit (128^3: 294 us a step; 310 at one wave with the next
+//   plane in registers).
 // Measured slower with the higher floor: MRT on D3Q7 (-16 %, 200 registers) and on D3Q19
 // with FP16, the third composition on D3Q7 with FP16, the general-curvature D3Q19 and
-// D2Q9 (FP16) kernels, the variable-density model on D2Q5 (BF16), and every kernel in
-// FP32 / FP64
+// D2Q9 (FP16) kernels, the variable-density model on D2Q5 (BF16), and every other kernel
+// in FP32 / FP64
 template <class SL, int PREC, int COLL, int NC = 2, int QF = 0>
 constexpr int lbm_waves() {
     constexpr bool s16 = PREC == P16 || PREC == PB16;

@@ -655,15 +655,18 @@ struct BlockPlan {
 
 // How a call of n steps is cut into windows: the estimate of the time per step in us,
 // smallest over the windows of both sizes (256 and 512 or 1024 nodes) of every power-of-two
-// width and up to 128 steps per launch.  A launch takes 3.1 us, each step its barriers
-// (0.3 us, 0.7 with flow), and a window its loads, collisions and stores: alone on a
-// compute unit the latency of these, else their throughput (the windows of all 256 units
-// share the memory: `mem`, with the part of a 128-byte line that a row's ends waste; the
-// collisions, `cmp`, overlap with it mostly where two windows share a unit).  The constants
-// are a fit to 900 timings (eight families, 64^2 to 2048^2): the choice is within 2 % of
-// the fastest on average.  The marching kernel stays where the estimate says so: large
-// boxes of the D2Q9 lattices with flow and 16-bit storage (2048^2: 156 us against 159), and
-// for states whose buoyancy needs the mean of every step.
+// width and up to 128 steps per launch.  A launch takes 4 us, each step its barriers
+// (0.36 us, 0.68 with flow), and a window its loads, collisions and stores: alone on a
+// compute unit the latency of these, else their throughput.  The windows of all 256 units
+// share the memory (`mem`, with the part of a 128-byte line that a row's ends waste, and
+// less while both copies stay in the last-level cache); the collisions, `cmp`, overlap with
+// it where several windows share a unit.  One window of 1024 nodes has a unit to itself, so
+// these run in whole rounds; one of 512 FP64 nodes with flow leaves part of a unit idle.
+// The constants are a fit to 1900 timings (ten families, 64^2 to 2047^2): the choice is
+// within 0.8 % of the fastest on average (6 % with a fit to fewer: 150 x 93 D2Q9 + 3 x D2Q5
+// FP32 closed 3.01 us a step, 2.71 now; 2047^2 D2Q9 BF16 68.1, 59.2 now; 512^2 D2Q9 + 3 x
+// D2Q5 FP64 18.5, 15.9 now).  The marching kernel stays where the estimate says so, and for
+// states whose buoyancy needs the mean of every step.
 BlockPlan block_plan(const lbm_handle* h, int64_t n) {
     const Layout& L = h->L;
     BlockPlan best;
@@ -671,7 +674,8 @@ BlockPlan block_plan(const lbm_handle* h, int64_t n) {
     const double nodes = double(L.nodes), flow = L.qf ? 1.0 : 0.0;
     const double bytes = double(L.copy_bytes) / nodes;  // of a node's populations
     const double word = bytes / L.nslots;
-    const double cmp = 0.0067 * L.nslots * (13.0 + 4.0 * flow);  // of 1024 nodes, one step
+    const double cmp = 0.0067 * L.nslots * (13.0 + 14.4 * flow);  // of 1024 nodes, one step
+    const double rate = 2.0 * bytes * nodes > 124e6 ? 33.7e3 : 47e3;  // bytes/us of one unit
     double cost = 3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 + (h->base.wall_x ? 5.0 : 0.0);
     for (int nt : h->ks->block_nt) {
         for (int lw = 4; (1 << lw) <= nt; ++lw) {
@@ -679,11 +683,14 @@ BlockPlan block_plan(const lbm_handle* h, int64_t n) {
                 BlockGeom g;
                 if (!block_geometry(L, nt, lw, k, g)) break;
                 const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
-                const double mem = bytes * 1024.0 / 42e3 *
-                                   (1.0 + 90.0 / ((1 << lw) * word) + share * (1.0 + 90.0 / (g.ix * word)));
-                const double alone = nt / 1024.0 * (2.0 + 0.6 * k * cmp);
-                const double busy = windows * nt / (256.0 * 1024.0) * (mem + (0.1 + 0.4 * flow) * k * cmp);
-                const double t = (3.1 + (0.3 + 0.4 * flow) * k + std::max(alone, busy)) / k;
+                const double mem = bytes * 1024.0 / rate *
+                                   (1.0 + 16.5 / ((1 << lw) * word) + share * (1.0 + 44.0 / (g.ix * word)));
+                const double alone = nt / 1024.0 * (0.44 + 0.456 * k * cmp);
+                double rounds = windows * nt / (256.0 * 1024.0);
+                if (nt == 1024 && rounds > 1.0) rounds = std::ceil(rounds);
+                if (nt > 256 && flow > 0.0 && word > 4.0) rounds *= 1.43;
+                const double busy = rounds * (mem + (0.395 - 0.087 * flow) * k * cmp);
+                const double t = (3.95 + (0.364 + 0.314 * flow) * k + std::max(alone, busy)) / k;
                 if (t < cost) {
                     cost = t;
                     best.nt = nt;
