@@ -665,8 +665,8 @@ struct BlockPlan {
 // The constants are a fit to 1900 timings (ten families, 64^2 to 2047^2): the choice is
 // within 0.8 % of the fastest on average (6 % with a fit to fewer: 150 x 93 D2Q9 + 3 x D2Q5
 // FP32 closed 3.01 us a step, 2.71 now; 2047^2 D2Q9 BF16 68.1, 59.2 now; 512^2 D2Q9 + 3 x
-// D2Q5 FP64 18.5, 15.9 now).  The marching kernel stays where the estimate says so, and for
-// states whose buoyancy needs the mean of every step.
+// D2Q5 FP64 18.5, 15.9 now).  The marching kernel stays where its own estimate is lower, and
+// for states whose buoyancy needs the mean of every step.
 BlockPlan block_plan(const lbm_handle* h, int64_t n) {
     const Layout& L = h->L;
     BlockPlan best;
@@ -676,7 +676,22 @@ BlockPlan block_plan(const lbm_handle* h, int64_t n) {
     const double word = bytes / L.nslots;
     const double cmp = 0.0067 * L.nslots * (13.0 + 14.4 * flow);  // of 1024 nodes, one step
     const double rate = 2.0 * bytes * nodes > 124e6 ? 33.7e3 : 47e3;  // bytes/us of one unit
-    double cost = 3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 + (h->base.wall_x ? 5.0 : 0.0);
+    // the marching kernel's time, and how much longer than the estimate the best windows take
+    // (`heavy`): with flow the collisions of the less usual models and the conversions of
+    // 16-bit storage count, most for boxes beyond the last-level cache (2048^2 D2Q9 + 3 x D2Q5,
+    // march / windows: BF16 112 / 109 us, FP16 116 / 128, BF16 with TRT 116 / 131; 1500^2, whose
+    // rows are not whole lines, BF16 74 / 52)
+    const bool s16 = word < 3.5, trt = h->cfg.collision == LBM_TRT;
+    const bool wide = h->cfg.collision == LBM_MRT || h->cfg.general_kappa;
+    double heavy = 1.0, march = L.whole ? 1.0 : (s16 ? 1.25 : 1.1);
+    if (flow > 0.0 && s16) {
+        heavy = (L.prec == LBM_FP32_FP16STORE ? 1.39 : 1.2) * (wide ? 1.3 : trt ? 1.15 : 1.0) *
+                (h->cfg.variable_density ? 1.125 : 1.0);
+        march *= wide ? 1.23 : 1.12;
+    } else if (flow > 0.0 && word > 6.0 && wide) {
+        heavy = 1.28;  // 2048^2 D2Q9 + 3 x D2Q5 FP64, MRT: 344 / 363 us
+    }
+    double cost = 1e30, loaded = 1e30;
     for (int nt : h->ks->block_nt) {
         for (int lw = 4; (1 << lw) <= nt; ++lw) {
             for (int k = 1; k <= 128 && k <= n; ++k) {
@@ -688,11 +703,16 @@ BlockPlan block_plan(const lbm_handle* h, int64_t n) {
                 const double alone = nt / 1024.0 * (0.44 + 0.456 * k * cmp);
                 double rounds = windows * nt / (256.0 * 1024.0);
                 if (nt == 1024 && rounds > 1.0) rounds = std::ceil(rounds);
-                if (nt > 256 && flow > 0.0 && word > 4.0) rounds *= 1.43;
-                const double busy = rounds * (mem + (0.395 - 0.087 * flow) * k * cmp);
-                const double t = (3.95 + (0.364 + 0.314 * flow) * k + std::max(alone, busy)) / k;
+                if (nt > 256 && flow > 0.0 && word > 6.0) rounds *= 1.43;
+                // 1024 nodes with TRT on the D2Q9 lattices spill 33 registers (512^2 BF16: 20 us
+                // a step, 15.5 with the marching kernel)
+                const double spill = trt && s16 && L.nslots > 30 && nt == 1024 ? 1.9 : 1.0;
+                const double busy = rounds * spill * (mem + (0.395 - 0.087 * flow) * k * cmp);
+                const double base = 3.95 + (0.364 + 0.314 * flow) * k;
+                const double t = (base + std::max(alone, busy)) / k;
                 if (t < cost) {
                     cost = t;
+                    loaded = (base + std::max(alone, busy * heavy)) / k;
                     best.nt = nt;
                     best.k = k;
                     best.g = g;
@@ -700,6 +720,7 @@ BlockPlan block_plan(const lbm_handle* h, int64_t n) {
             }
         }
     }
+    if (loaded >= 3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 * march + (h->base.wall_x ? 5.0 : 0.0)) best.nt = 0;
     return best;
 }
 
