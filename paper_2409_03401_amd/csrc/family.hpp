@@ -31,7 +31,7 @@ struct Family {
                         hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP_PHI, PREC, NT, false, COLL>), g, block, 0, s, kp);
                         break;
                     }
-                if constexpr (NC == 2)
+                if constexpr (NC == 2)  // lbm_step_external asks it of two compositions only
                     hipLaunchKernelGGL((k_lbm<SL, FL, MODE_STEP_PHI, PREC, NT, true, COLL>), g, block, 0, s, kp);
                 break;
             case MODE_SCALARS:

@@ -951,7 +951,12 @@ int lbm_step_external(lbm_handle* h, const void* src, void* dst, void* phi_src, 
     kp.phi_ref = ref_in;
     // the buffered <phi> is recomputed with the mean subtraction, else carried over
     kp.ref_copy = h->cfg.gravity_mean_subtract ? nullptr : ref_out;
-    const int groups = launch_fused(h, phi_src ? MODE_STEP_PHI : MODE_STEP, h->L.gen_steps || (phi_src && !h->ks->adj_step), kp, s);
+    // a third composition has no adjoint and no step that writes phi as well: phi is formed first
+    const bool with_phi = phi_src && h->L.nc == 2;
+    if (phi_src && !with_phi)
+        if (int r = lbm_phase_field(h, src, phi_src, stream)) return r;
+    const int groups = launch_fused(h, with_phi ? MODE_STEP_PHI : MODE_STEP,
+                                    h->L.gen_steps || (with_phi && !h->ks->adj_step), kp, s);
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
     for (int a = 0; a < 2; ++a)
         if (walls[a]) h->ks->walls(kp, a, s);
