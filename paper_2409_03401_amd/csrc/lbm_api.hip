@@ -736,8 +736,11 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     set_slots(h, kp[1], h->copy[1], h->copy[0]);
     if (BlockPlan plan = block_plan(h, nsteps); plan.nt) {
         // 2D: several steps per launch, cut evenly; the x walls are exchanged (k_walls) for
-        // the state that the call leaves only
-        const int64_t launches = (nsteps + plan.k - 1) / plan.k;
+        // the state that the call leaves only.  An even number of launches for an even number
+        // of steps: the state then ends in the copy where it began, as with one step per
+        // launch, and a call recorded in a graph goes on from its own result when replayed
+        int64_t launches = (nsteps + plan.k - 1) / plan.k;
+        launches += (launches ^ nsteps) & 1;
         for (int64_t i = 0; i < launches; ++i) {
             plan.g.nsub = int(nsteps * (i + 1) / launches - nsteps * i / launches);
             plan.g.raw_x = i > 0;
