@@ -33,8 +33,11 @@ void launch_sum6(const double* partials, int nparts, double* out, bool accumulat
 }
 
 void launch_euler(const unsigned char* mask, const EulerGeom& g, double* partials, int nblocks, hipStream_t s) {
-    if (g.d == 3) hipLaunchKernelGGL((k_euler<3>), dim3(nblocks), dim3(256), 0, s, mask, g, partials);
-    else hipLaunchKernelGGL((k_euler<2>), dim3(nblocks), dim3(256), 0, s, mask, g, partials);
+    using Long = unsigned long long;
+    const dim3 grid(nblocks), block(256);
+    if (g.d == 2) hipLaunchKernelGGL((k_euler<2, unsigned>), grid, block, 0, s, mask, g, partials);  // at most 2^31 anchors
+    else if (!g.wide(256LL * nblocks)) hipLaunchKernelGGL((k_euler<3, unsigned>), grid, block, 0, s, mask, g, partials);
+    else hipLaunchKernelGGL((k_euler<3, Long>), grid, block, 0, s, mask, g, partials);
 }
 
 void launch_zero(double* p, long long n, hipStream_t s) {

@@ -7,6 +7,8 @@
 
 #include <cstdint>
 
+#include "euler.hpp"
+
 namespace lbm {
 
 // threads of a 3D work-group, and the largest tile with its ring of one node (the host
@@ -141,18 +143,6 @@ constexpr int kAuxCRows = 3;
 // the x walls (left by a launch of this kernel), else exchanged ones (k_walls).
 struct BlockGeom {
     int lw, hx, hz, ix, iz, tiles_x, tiles_z, full_x, full_z, nsub, raw_x;
-};
-
-// Euler characteristic of the closed cells of a node mask (droplet count of
-// Section 4.2.2).  Only the d active axes of the run are listed: axis i has n[i]
-// cells, mask stride stride[i], wall[i] != 0 when it ends at walls.  An anchor
-// j_i in [0, n[i] + wall[i]) stands for the vertex position between cells j_i - 1
-// and j_i and for cell j_i (when j_i < n[i]); nanchors = prod(n[i] + wall[i]).
-struct EulerGeom {
-    int d;
-    int n[3], wall[3];
-    long long stride[3];
-    long long nanchors;
 };
 
 }  // namespace lbm
