@@ -33,27 +33,6 @@
 
 namespace lbm {
 
-// LDS bytes of a window of nt nodes: the moving populations in their stored form, and phi
-template <class SL, class FL, int PREC, int NC>
-constexpr int block_lds(int nt) {
-    using SLOTS = Slots<FL::Q, SL::Q, NC>;
-    constexpr int nrest = (FL::Q > 0 ? 1 : 0) + 1 + NC;
-    constexpr int word = PREC == P64 ? 8 : PREC == P32 ? 4 : 2;
-    return nt * ((SLOTS::N - nrest) * word + (FL::Q > 0 ? int(sizeof(typename Stor<PREC>::C)) : 0));
-}
-
-// threads of the large window.  Without flow 512: two or three of them share a compute unit
-// and one loads while another collides (2048^2 D2Q5 FP32 46 us a step against 49 with 1024;
-// D2Q9 FP32 75 against 85, BF16 69 against 73).  With flow each step costs two rings, so the
-// share of the window that is owned matters more: 1024 where the populations fit in LDS and
-// in a quarter of the registers (2048^2 D2Q9 + 3 x D2Q9 FP32 221 us against 304 with 512).
-template <class SL, class FL, int PREC, int COLL, int NC>
-constexpr int block_threads() {
-    constexpr int regs = Slots<FL::Q, SL::Q, NC>::N * int(sizeof(typename Stor<PREC>::C)) / 4;
-    constexpr int most = (COLL & (COLL_MRT | COLL_GK)) != 0 ? 30 : 36;  // these need more temporaries
-    return (FL::Q > 0 && regs <= most && block_lds<SL, FL, PREC, NC>(1024) <= 160 * 1024) ? 1024 : 512;
-}
-
 template <class SL, class FL, int PREC, int NT, int COLL = COLL_BGK, int NC = 2>
 __global__ void __launch_bounds__(NT) k_block(const KParams P, const BlockGeom B) {
     using NODE = Node<SL, FL, PREC, COLL, NC>;
@@ -67,7 +46,7 @@ __global__ void __launch_bounds__(NT) k_block(const KParams P, const BlockGeom B
     static_assert(SL::DIM == 2, "2D windows");
     using LW = typename std::conditional<S16, unsigned short, C>::type;  // stored form of a moving population
     constexpr int NM = N - ((FLOW ? 1 : 0) + 1 + NC);                    // moving populations
-    static_assert(block_lds<SL, FL, PREC, NC>(NT) <= 160 * 1024, "window too large for LDS");
+    static_assert(window_lds(FL::Q, SL::Q, PREC, NC, NT) <= 160 * 1024, "window too large for LDS");
 
     __shared__ LW spop[NM * NT];
     __shared__ C sphi[FLOW ? NT : 1];

@@ -102,22 +102,18 @@ struct Family {
     }
     // the narrow row segments (LBM_TILE) march one step per launch
     static constexpr bool kBlock = SL::DIM == 2 && NT == 256;
-    static constexpr int kSmall = 256;
-    static constexpr int large() {
-        if constexpr (kBlock) return block_threads<SL, FL, PREC, COLL, NC>();
-        else return 0;
-    }
+    static constexpr int kSmall = kSmallWindow, kLarge = kBlock ? large_window(FL::Q, SL::Q, PREC, COLL, NC) : 0;
     static void block(int nt, unsigned grid, const KParams& kp, const BlockGeom& g, hipStream_t s) {
         if constexpr (kBlock) {
             if (nt == kSmall) hipLaunchKernelGGL((k_block<SL, FL, PREC, kSmall, COLL, NC>), dim3(grid), dim3(kSmall), 0, s, kp, g);
-            else hipLaunchKernelGGL((k_block<SL, FL, PREC, large(), COLL, NC>), dim3(grid), dim3(large()), 0, s, kp, g);
+            else hipLaunchKernelGGL((k_block<SL, FL, PREC, kLarge, COLL, NC>), dim3(grid), dim3(kLarge), 0, s, kp, g);
         }
     }
     static constexpr KernelSet set{&fused, &init, &get_pops, &set_pops, &walls,
                                    kAdj ? &adj_step : nullptr, kAdj ? &adj_seed : nullptr,
                                    kAdj ? &adj_gather : nullptr, kAdj ? &adj_init_local : nullptr,
                                    kAdj ? &adj_copy : nullptr, NT,
-                                   kBlock ? &block : nullptr, {kBlock ? kSmall : 0, large()}};
+                                   kBlock ? &block : nullptr, {kBlock ? kSmall : 0, kLarge}};
 };
 
 template <class SL, class FL, int NT>

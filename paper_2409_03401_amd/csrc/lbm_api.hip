@@ -313,10 +313,9 @@ int check_config(const lbm_config* c, Layout* L) {
         L->gen = make_tiles(*L, want_tx, want_ty);
     }
     // Without the phi stencil (no flow, or moments of the scalars alone) a plane needs
-    // nothing of the one before: in 3D one plane per work-group, two on large grids, so that
-    // the loads of many groups overlap (96^3 FP64 step 67.2 -> 61.2 us, 256^3 FP32 580 ->
-    // 550 us against the chunks above; 2D rows measured the same either way)
-    L->zc_flat = L->dim == 2 || L->tuned ? 0 : (L->line.gx * L->line.gy * (long long)L->NZ > 8192 ? 2 : 1);
+    // nothing of the one before: in 3D short chunks, so that the loads of many groups overlap
+    // (2D rows measured the same either way)
+    L->zc_flat = L->dim == 2 || L->tuned ? 0 : flat_chunk((long long)L->line.gx * L->line.gy, L->NZ, L->ks->nt);
     // The general kernel where its plain stores or its tiles are worth its registers: rows
     // that are not whole lines (87 x 123 x 70 FP64, D3Q19 scalars 276 us a step against 338),
     // and whole rows of a width that 64 does not divide, in 3D
@@ -490,6 +489,18 @@ int launched(const char* what) {
     return LBM_OK;
 }
 
+// Windows of a 2D call of n steps (nt = 0: the marching kernel, which also takes the states
+// whose buoyancy needs the mean of every step)
+BlockPlan plan_call(const lbm_handle* h, int64_t n) {
+    const Layout& L = h->L;
+    const lbm_config& c = h->cfg;
+    if (!h->ks->block || L.tuned || c.gravity_mean_subtract) return BlockPlan{};
+    const int coll = (c.collision == LBM_TRT ? COLL_TRT : c.collision == LBM_MRT ? COLL_MRT : 0) |
+                     (c.variable_density ? COLL_VD : 0) | (c.general_kappa ? COLL_GK : 0);
+    return block_plan(PlanInput{L.NX, L.NZ, L.qf, L.nslots, L.prec, double(L.copy_bytes), L.whole, h->base.wall_x != 0,
+                                coll, {h->ks->block_nt[0], h->ks->block_nt[1]}}, n);
+}
+
 }  // namespace
 
 extern "C" {
@@ -628,104 +639,6 @@ int lbm_init_composition(const lbm_config* cfg, void* state, size_t state_bytes,
     return init_impl(cfg, state, state_bytes, phi0, c, mu, 2, stream, out);
 }
 
-namespace {
-
-// windows of nt nodes, 2^lw wide, for up to k steps per launch; false: the halo leaves none
-bool block_geometry(const Layout& L, int nt, int lw, int k, BlockGeom& g) {
-    const int bw = 1 << lw, bh = nt >> lw;
-    const int halo = L.qf ? 2 * k - 1 : k - 1;
-    g = BlockGeom{};
-    g.lw = lw;
-    g.full_x = L.NX <= bw;
-    g.full_z = L.NZ <= bh;
-    g.hx = g.full_x ? 0 : halo;
-    g.hz = g.full_z ? 0 : halo;
-    g.ix = g.full_x ? L.NX : bw - 2 * halo;
-    g.iz = g.full_z ? L.NZ : bh - 2 * halo;
-    if (g.ix < 1 || g.iz < 1) return false;
-    g.tiles_x = (L.NX + g.ix - 1) / g.ix;
-    g.tiles_z = (L.NZ + g.iz - 1) / g.iz;
-    return true;
-}
-
-struct BlockPlan {
-    int nt = 0, k = 0;  // nt = 0: one step per launch with the marching kernel
-    BlockGeom g;
-};
-
-// How a call of n steps is cut into windows: the estimate of the time per step in us,
-// smallest over the windows of both sizes (256 and 512 or 1024 nodes) of every power-of-two
-// width and up to 128 steps per launch.  A launch takes 4 us, each step its barriers
-// (0.36 us, 0.68 with flow), and a window its loads, collisions and stores: alone on a
-// compute unit the latency of these, else their throughput.  The windows of all 256 units
-// share the memory (`mem`, with the part of a 128-byte line that a row's ends waste, and
-// less while both copies stay in the last-level cache); the collisions, `cmp`, overlap with
-// it where several windows share a unit.  One window of 1024 nodes has a unit to itself, so
-// these run in whole rounds; one of 512 FP64 nodes with flow leaves part of a unit idle.
-// The constants are a fit to 1900 timings (ten families, 64^2 to 2047^2): the choice is
-// within 0.8 % of the fastest on average (6 % with a fit to fewer: 150 x 93 D2Q9 + 3 x D2Q5
-// FP32 closed 3.01 us a step, 2.71 now; 2047^2 D2Q9 BF16 68.1, 59.2 now; 512^2 D2Q9 + 3 x
-// D2Q5 FP64 18.5, 15.9 now).  The marching kernel stays where its own estimate is lower, and
-// for states whose buoyancy needs the mean of every step.
-BlockPlan block_plan(const lbm_handle* h, int64_t n) {
-    const Layout& L = h->L;
-    BlockPlan best;
-    if (!h->ks->block || L.tuned || h->cfg.gravity_mean_subtract) return best;
-    const double nodes = double(L.nodes), flow = L.qf ? 1.0 : 0.0;
-    const double bytes = double(L.copy_bytes) / nodes;  // of a node's populations
-    const double word = bytes / L.nslots;
-    const double cmp = 0.0067 * L.nslots * (13.0 + 14.4 * flow);  // of 1024 nodes, one step
-    const double rate = 2.0 * bytes * nodes > 124e6 ? 33.7e3 : 47e3;  // bytes/us of one unit
-    // the marching kernel's time, and how much longer than the estimate the best windows take
-    // (`heavy`): with flow the collisions of the less usual models and the conversions of
-    // 16-bit storage count, most for boxes beyond the last-level cache (2048^2 D2Q9 + 3 x D2Q5,
-    // march / windows: BF16 112 / 109 us, FP16 116 / 128, BF16 with TRT 116 / 131; 1500^2, whose
-    // rows are not whole lines, BF16 74 / 52)
-    const bool s16 = word < 3.5, trt = h->cfg.collision == LBM_TRT;
-    const bool wide = h->cfg.collision == LBM_MRT || h->cfg.general_kappa;
-    double heavy = 1.0, march = L.whole ? 1.0 : (s16 ? 1.25 : 1.1);
-    if (flow > 0.0 && s16) {
-        heavy = (L.prec == LBM_FP32_FP16STORE ? 1.39 : 1.2) * (wide ? 1.3 : trt ? 1.15 : 1.0) *
-                (h->cfg.variable_density ? 1.125 : 1.0);
-        march *= wide ? 1.23 : 1.12;
-    } else if (flow > 0.0 && word > 6.0 && wide) {
-        heavy = 1.28;  // 2048^2 D2Q9 + 3 x D2Q5 FP64, MRT: 344 / 363 us
-    }
-    double cost = 1e30, loaded = 1e30;
-    for (int nt : h->ks->block_nt) {
-        for (int lw = 4; (1 << lw) <= nt; ++lw) {
-            for (int k = 1; k <= 128 && k <= n; ++k) {
-                BlockGeom g;
-                if (!block_geometry(L, nt, lw, k, g)) break;
-                const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
-                const double mem = bytes * 1024.0 / rate *
-                                   (1.0 + 16.5 / ((1 << lw) * word) + share * (1.0 + 44.0 / (g.ix * word)));
-                const double alone = nt / 1024.0 * (0.44 + 0.456 * k * cmp);
-                double rounds = windows * nt / (256.0 * 1024.0);
-                if (nt == 1024 && rounds > 1.0) rounds = std::ceil(rounds);
-                if (nt > 256 && flow > 0.0 && word > 6.0) rounds *= 1.43;
-                // 1024 nodes with TRT on the D2Q9 lattices spill 33 registers (512^2 BF16: 20 us
-                // a step, 15.5 with the marching kernel)
-                const double spill = trt && s16 && L.nslots > 30 && nt == 1024 ? 1.9 : 1.0;
-                const double busy = rounds * spill * (mem + (0.395 - 0.087 * flow) * k * cmp);
-                const double base = 3.95 + (0.364 + 0.314 * flow) * k;
-                const double t = (base + std::max(alone, busy)) / k;
-                if (t < cost) {
-                    cost = t;
-                    loaded = (base + std::max(alone, busy * heavy)) / k;
-                    best.nt = nt;
-                    best.k = k;
-                    best.g = g;
-                }
-            }
-        }
-    }
-    if (loaded >= 3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 * march + (h->base.wall_x ? 5.0 : 0.0)) best.nt = 0;
-    return best;
-}
-
-}  // namespace
-
 int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     if (int r = check_handle(h)) return r;
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps < 0");
@@ -734,7 +647,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     KParams kp[2] = {h->base, h->base};
     set_slots(h, kp[0], h->copy[0], h->copy[1]);
     set_slots(h, kp[1], h->copy[1], h->copy[0]);
-    if (BlockPlan plan = block_plan(h, nsteps); plan.nt) {
+    if (BlockPlan plan = plan_call(h, nsteps); plan.nt) {
         // 2D: several steps per launch, cut evenly; the x walls are exchanged (k_walls) for
         // the state that the call leaves only.  An even number of launches for an even number
         // of steps: the state then ends in the copy where it began, as with one step per

@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "euler.hpp"
+#include "plan.hpp"
 
 namespace lbm {
 
@@ -25,15 +26,9 @@ constexpr int kMaxSlots = 19 + 3 * 19;
 constexpr int kNumMom = 11;
 constexpr int kNumDiag = 8;
 
-enum Prec : int { P64 = 0, P32 = 1, P16 = 2, PB16 = 3 };
 // MODE_STEP_PHI: a step that also writes phi of its source state (P.phi_out)
 // MODE_SCALARS: moments other than pressure and velocity (they need neither f nor the stencil)
 enum Mode : int { MODE_STEP = 0, MODE_MOMENTS = 1, MODE_DIAG = 2, MODE_STEP_PHI = 3, MODE_SCALARS = 4 };
-// collision operator of the fused step: the paper's BGK, or two relaxation times
-// (flags): COLL_TRT two relaxation times, COLL_VD the variable-density flow model
-// COLL_GK general curvature matrices of the free energies (2 x 2 closure per node)
-// COLL_MRT multiple relaxation times on the lattice's moment basis
-enum Coll : int { COLL_BGK = 0, COLL_TRT = 1, COLL_VD = 2, COLL_GK = 4, COLL_MRT = 8 };
 
 // Storage traits.  FP64 / FP32 store every population as is.  The 16-bit
 // formats store the moving populations (k != 0) as d = (x - w_k ref) * 2^s in
@@ -136,13 +131,5 @@ struct KParams {
 
 constexpr int kAuxRows = 7;  // per-step scratch rows of the adjoint (c_F rows apart)
 constexpr int kAuxCRows = 3;
-
-// Windows of the several-steps kernel (2D): 2^lw nodes wide, halo (hx, hz), owned nodes
-// ix x iz per window; full_*: the axis fits into the window whole (no halo, wraps inside).
-// nsub: steps per launch.  raw_x: the source copy holds raw post-collision populations at
-// the x walls (left by a launch of this kernel), else exchanged ones (k_walls).
-struct BlockGeom {
-    int lw, hx, hz, ix, iz, tiles_x, tiles_z, full_x, full_z, nsub, raw_x;
-};
 
 }  // namespace lbm

@@ -1,0 +1,34 @@
+"""CPU checks of the launch plans (csrc/plan.hpp)."""
+
+import random
+
+import pytest
+
+import plan_program as plans
+
+pytestmark = pytest.mark.skipif(not plans.available(), reason="no C++ compiler")
+
+MAX_THREADS = 2**32 - 1  # of a launch along one axis of its grid
+
+
+def _call(nx, ny, n, prec="fp32", qf=0, qs=5, nc=2, wall_x=False, coll=0):
+    return dict(nx=nx, ny=ny, n=n, prec=prec, qf=qf, qs=qs, nc=nc, wall_x=wall_x, coll=coll)
+
+
+def test_flat_chunks_fit_a_launch():
+    # up to 2^30 - 1 nodes in one column of tiles, and in many columns
+    grids = [(1, 2**24 - 1), (1, 2**24), (1, 2**25 - 2), (1, 2**25), (1, 2**30 - 1), (2, 2**24), (64, 2**20 - 1),
+             (2**22, 8), (512, 512), (50, 96), (1, 1)]
+    for (cols, nz), zc in zip(grids, plans.flat_chunks(grids)):
+        assert zc == 0 or cols * -(-nz // zc) * 256 <= MAX_THREADS, (cols, nz, zc)
+    # ordinary grids keep their short chunks
+    assert plans.flat_chunks([(50, 96), (512, 512)]) == [1, 2]
+
+
+def test_windows_fit_a_launch():
+    # long narrow boxes, whose windows hold lanes beyond the box, and boxes of many halos
+    calls = [_call(nx, (2**30 - 1) // nx, n, prec, qf, qs, wall_x=wall)
+             for nx in (1, 2, 3, 4, 5, 8, 16, 17, 1000, 32767) for n in (1, 5, 100)
+             for prec, qf, qs in (("fp32", 0, 5), ("bf16", 9, 5), ("bf16", 0, 9)) for wall in (False, True)]
+    for c, p in zip(calls, plans.windows(calls)):
+        assert p["nt"] * p["tiles_x"] * p["tiles_z"] <= MAX_THREADS, (c, p)
