@@ -655,7 +655,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
         int64_t launches = (nsteps + plan.k - 1) / plan.k;
         launches += (launches ^ nsteps) & 1;
         for (int64_t i = 0; i < launches; ++i) {
-            plan.g.nsub = int(nsteps * (i + 1) / launches - nsteps * i / launches);
+            plan.g.nsub = int(steps_of_launch(nsteps, launches, i));
             plan.g.raw_x = i > 0;
             h->ks->block(plan.nt, unsigned(plan.g.tiles_x) * unsigned(plan.g.tiles_z), kp[h->cur], plan.g, s);
             if (i == launches - 1 && h->base.wall_x) h->ks->walls(kp[h->cur], 0, s);

@@ -82,6 +82,11 @@ inline bool block_geometry(const PlanInput& in, int nt, int lw, int k, BlockGeom
     return true;
 }
 
+// steps of launch i of `launches` that share n steps
+constexpr long long steps_of_launch(long long n, long long launches, long long i) {
+    return n / launches + (i < n % launches ? 1 : 0);
+}
+
 struct BlockPlan {
     int nt = 0, k = 0;  // nt = 0: one step per launch with the marching kernel
     BlockGeom g;

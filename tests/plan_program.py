@@ -22,6 +22,9 @@ int main() {
         if (what == 'f') {  // chunk of the 3D kernels without the stencil
             if (std::scanf("%lld %lld", &cols, &nz) != 2) return 1;
             std::printf("%d\n", flat_chunk(cols, nz, 256));
+        } else if (what == 'n') {  // steps of a launch
+            if (std::scanf("%lld %lld %lld", &n, &cols, &nz) != 3) return 1;
+            std::printf("%lld\n", steps_of_launch(n, cols, nz));
         } else {  // windows of a 2D call
             if (std::scanf("%d %d %d %d %d %d %lf %d %d %d %lld", &in.nx, &in.nz, &in.qf, &qs, &nc, &in.prec,
                            &in.copy_bytes, &whole, &wall_x, &in.coll, &n) != 11) return 1;
@@ -67,6 +70,11 @@ def _ask(lines):
 def flat_chunks(grids):
     """Chunk length for every (columns, planes)."""
     return [r[0] for r in _ask([f"f {c} {n}" for c, n in grids])]
+
+
+def steps_of_launch(launches):
+    """Steps of every (steps of the call, launches, index of the launch)."""
+    return [r[0] for r in _ask([f"n {n} {m} {i}" for n, m, i in launches])]
 
 
 def windows(calls):

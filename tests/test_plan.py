@@ -32,3 +32,14 @@ def test_windows_fit_a_launch():
              for prec, qf, qs in (("fp32", 0, 5), ("bf16", 9, 5), ("bf16", 0, 9)) for wall in (False, True)]
     for c, p in zip(calls, plans.windows(calls)):
         assert p["nt"] * p["tiles_x"] * p["tiles_z"] <= MAX_THREADS, (c, p)
+
+
+def test_steps_of_a_launch():
+    """The launches share the steps evenly, also of a call so long that steps times launches
+    passes 2^63."""
+    cases = [(n, m, i) for n in (1, 2, 7, 200, 10**11, 2**62 + 1) for m in (1, 2, 7, n // 128 + 1)
+             if m <= n for i in {0, 1, m // 2, m - 1} if i < m]
+    for (n, m, i), steps in zip(cases, plans.steps_of_launch(cases)):
+        assert n // m <= steps <= -(-n // m), (n, m, i, steps)
+    for n, m in ((1, 1), (7, 3), (200, 7), (1000, 1000)):
+        assert sum(plans.steps_of_launch([(n, m, i) for i in range(m)])) == n
