@@ -76,11 +76,7 @@ struct Layout {
 // the fewest tiles, weighed with the lines that a tile's rows and ring touch (100 x 75 x 50
 // FP16: 50 x 5 28.1 us, 100 x 2 28.5, 64 x 4 30.6).
 void tile_shape(const Layout& L, int& tx, int& ty) {
-    auto fits = [](int w, int h) {
-        return w >= 1 && h >= 1 && w * h <= kTileNodes && (w + 2) * (h + 2) <= kTileCells &&
-               2 * (w + 2) + 2 * h <= kTileNodes;
-    };
-    if (tx && fits(tx, ty)) return;
+    if (tx && tile_fits(tx, ty)) return;
     tx = kTileX;
     ty = kTileY;
     if (L.whole && L.NX % kTileX == 0) return;
@@ -92,7 +88,7 @@ void tile_shape(const Layout& L, int& tx, int& ty) {
         if (nx > 1 && w < 32) break;
         if (nx > 1 && w < 48 && !fit) continue;
         int h = std::min(L.NY, kTileNodes / w);
-        while (h > 0 && !fits(w, h)) --h;
+        while (h > 0 && !tile_fits(w, h)) --h;
         if (h < 1) continue;
         const int ny = (L.NY + h - 1) / h;
         h = (L.NY + ny - 1) / ny;

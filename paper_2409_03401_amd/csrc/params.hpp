@@ -12,10 +12,6 @@
 
 namespace lbm {
 
-// threads of a 3D work-group, and the largest tile with its ring of one node (the host
-// keeps tile_x tile_y <= kTileNodes, (tile_x + 2) (tile_y + 2) <= kTileCells and
-// 2 (tile_x + 2) + 2 tile_y <= kTileNodes: one ring node per thread)
-constexpr int kTileNodes = 256, kTileCells = 464;
 // the tile of grids whose rows are whole lines
 constexpr int kTileX = 64, kTileY = 4;
 // D3Q19 fluid + 3 x D3Q19 scalars (the paper's lattices), or D3Q19 + 4 x D3Q7 (a third

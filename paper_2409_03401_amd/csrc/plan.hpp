@@ -16,6 +16,14 @@ enum Coll : int { COLL_BGK = 0, COLL_TRT = 1, COLL_VD = 2, COLL_GK = 4, COLL_MRT
 // a launch takes fewer than 2^32 threads along an axis of its grid
 constexpr long long kMaxThreads = 0xFFFFFFFFLL;
 
+// threads of a 3D work-group, and the largest tile with its ring of one node
+constexpr int kTileNodes = 256, kTileCells = 464;
+// a tile of w x h nodes that a 3D work-group can take: one node and one ring node per thread
+constexpr bool tile_fits(int w, int h) {
+    return w >= 1 && h >= 1 && w <= kTileNodes && h <= kTileNodes && w * h <= kTileNodes &&
+           (w + 2) * (h + 2) <= kTileCells && 2 * (w + 2) + 2 * h <= kTileNodes;
+}
+
 // planes per work-group of the 3D kernels without the phi stencil, for `cols` columns of
 // tiles: one, two on large grids (96^3 FP64 step 67.2 -> 61.2 us, 256^3 FP32 580 -> 550 us
 // against the chunks of the other kernels); 0, those chunks, where the launch would be too

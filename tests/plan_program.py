@@ -22,6 +22,10 @@ int main() {
         if (what == 'f') {  // chunk of the 3D kernels without the stencil
             if (std::scanf("%lld %lld", &cols, &nz) != 2) return 1;
             std::printf("%d\n", flat_chunk(cols, nz, 256));
+        } else if (what == 't') {  // does a tile fit
+            int w, h;
+            if (std::scanf("%d %d", &w, &h) != 2) return 1;
+            std::printf("%d\n", int(tile_fits(w, h)));
         } else if (what == 'n') {  // steps of a launch
             if (std::scanf("%lld %lld %lld", &n, &cols, &nz) != 3) return 1;
             std::printf("%lld\n", steps_of_launch(n, cols, nz));
@@ -70,6 +74,11 @@ def _ask(lines):
 def flat_chunks(grids):
     """Chunk length for every (columns, planes)."""
     return [r[0] for r in _ask([f"f {c} {n}" for c, n in grids])]
+
+
+def tile_fits(tiles):
+    """Whether a 3D work-group can take every (width, height)."""
+    return [bool(r[0]) for r in _ask([f"t {w} {h}" for w, h in tiles])]
 
 
 def steps_of_launch(launches):

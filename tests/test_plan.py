@@ -25,6 +25,15 @@ def test_flat_chunks_fit_a_launch():
     assert plans.flat_chunks([(50, 96), (512, 512)]) == [1, 2]
 
 
+def test_tiles_that_fit():
+    """A tile given in the environment is taken only when its nodes and its ring fit, also
+    where the products of its sides pass 2^32."""
+    tiles = [(64, 4), (32, 8), (50, 5), (1, 125), (123, 1), (64, 5), (0, 4), (4, -1), (2**30, 4), (4, 2**30),
+             (2**31 - 1, 1), (2**16, 2**16), (2**16 + 1, 2**16 - 1)]
+    want = [w > 0 and h > 0 and w * h <= 256 and (w + 2) * (h + 2) <= 464 and 2 * (w + 2) + 2 * h <= 256 for w, h in tiles]
+    assert plans.tile_fits(tiles) == want
+
+
 def test_windows_fit_a_launch():
     # long narrow boxes, whose windows hold lanes beyond the box, and boxes of many halos
     calls = [_call(nx, (2**30 - 1) // nx, n, prec, qf, qs, wall_x=wall)
