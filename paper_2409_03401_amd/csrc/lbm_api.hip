@@ -645,16 +645,12 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     set_slots(h, kp[1], h->copy[1], h->copy[0]);
     if (BlockPlan plan = plan_call(h, nsteps); plan.nt) {
         // 2D: several steps per launch, cut evenly; the x walls are exchanged (k_walls) for
-        // the state that the call leaves only.  An even number of launches for an even number
-        // of steps: the state then ends in the copy where it began, as with one step per
-        // launch, and a call recorded in a graph goes on from its own result when replayed
-        int64_t launches = (nsteps + plan.k - 1) / plan.k;
-        launches += (launches ^ nsteps) & 1;
-        for (int64_t i = 0; i < launches; ++i) {
-            plan.g.nsub = int(steps_of_launch(nsteps, launches, i));
+        // the state that the call leaves only
+        for (int64_t i = 0; i < plan.launches; ++i) {
+            plan.g.nsub = int(steps_of_launch(nsteps, plan.launches, i));
             plan.g.raw_x = i > 0;
             h->ks->block(plan.nt, unsigned(plan.g.tiles_x) * unsigned(plan.g.tiles_z), kp[h->cur], plan.g, s);
-            if (i == launches - 1 && h->base.wall_x) h->ks->walls(kp[h->cur], 0, s);
+            if (i == plan.launches - 1 && h->base.wall_x) h->ks->walls(kp[h->cur], 0, s);
             if (int r = launched("block kernel")) return r;
             h->cur ^= 1;
             h->steps += plan.g.nsub;

@@ -95,14 +95,24 @@ constexpr long long steps_of_launch(long long n, long long launches, long long i
     return n / launches + (i < n % launches ? 1 : 0);
 }
 
+// launches of a call of n steps with at most k steps each: an even number for an even number
+// of steps, so that the state ends in the copy where it began, as with one step per launch
+// (a call recorded in a graph goes on from its own result when replayed)
+constexpr long long launches_of(long long n, int k) {
+    const long long l = (n + k - 1) / k;
+    return l + ((l ^ n) & 1);
+}
+
 struct BlockPlan {
-    int nt = 0, k = 0;  // nt = 0: one step per launch with the marching kernel
+    int nt = 0;  // 0: one step per launch with the marching kernel
+    long long launches = 0;
     BlockGeom g;
 };
 
-// How a call of n steps is cut into windows: the estimate of the time per step in us,
-// smallest over the windows of both sizes (256 and 512 or 1024 nodes) of every power-of-two
-// width and up to 128 steps per launch.  A launch takes 4 us, each step its barriers
+// How a call of n steps is cut into windows: the estimate of its time in us, smallest over
+// the windows of both sizes (256 and 512 or 1024 nodes) of every power-of-two width and the
+// numbers of launches that the call can take with up to 128 steps each.  The windows are those
+// of the steps that are run, ceil(n / launches).  A launch takes 4 us, each step its barriers
 // (0.36 us, 0.68 with flow), and a window its loads, collisions and stores: alone on a
 // compute unit the latency of these, else their throughput.  The windows of all 256 units
 // share the memory (`mem`, with the part of a 128-byte line that a row's ends waste, and
@@ -135,14 +145,23 @@ inline BlockPlan block_plan(const PlanInput& in, long long n) {
     } else if (flow > 0.0 && word > 6.0 && wide) {
         heavy = 1.28;  // 2048^2 D2Q9 + 3 x D2Q5 FP64, MRT: 344 / 363 us
     }
-    double cost = 1e30, loaded = 1e30;
+    // the longest launch of every way to share the steps among fewer launches
+    int longest[128], ways = 0;
+    for (int k = int(std::min(n, 128LL)); k > 0; --k) {
+        const long long launches = launches_of(n, k);
+        k = int((n + launches - 1) / launches);
+        longest[ways++] = k;
+    }
+    double cost = 1e30, loaded = 1e30;  // of the call
     for (int nt : in.nt) {
         for (int lw = 4; (1 << lw) <= nt; ++lw) {
-            for (int k = 1; k <= 128 && k <= n; ++k) {
+            for (int i = ways - 1; i >= 0; --i) {
                 BlockGeom g;
-                if (!block_geometry(in, nt, lw, k, g)) break;
+                if (!block_geometry(in, nt, lw, longest[i], g)) break;
                 const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
                 if (windows * nt > double(kMaxThreads)) break;  // more with every further step
+                const long long launches = launches_of(n, longest[i]);
+                const double k = double(n) / double(launches);
                 const double mem = bytes * 1024.0 / rate *
                                    (1.0 + 16.5 / ((1 << lw) * word) + share * (1.0 + 44.0 / (g.ix * word)));
                 const double alone = nt / 1024.0 * (0.44 + 0.456 * k * cmp);
@@ -154,18 +173,21 @@ inline BlockPlan block_plan(const PlanInput& in, long long n) {
                 const double spill = trt && s16 && in.nslots > 30 && nt == 1024 ? 1.9 : 1.0;
                 const double busy = rounds * spill * (mem + (0.395 - 0.087 * flow) * k * cmp);
                 const double base = 3.95 + (0.364 + 0.314 * flow) * k;
-                const double t = (base + std::max(alone, busy)) / k;
+                const double t = double(launches) * (base + std::max(alone, busy));
                 if (t < cost) {
                     cost = t;
-                    loaded = (base + std::max(alone, busy * heavy)) / k;
+                    loaded = double(launches) * (base + std::max(alone, busy * heavy));
                     best.nt = nt;
-                    best.k = k;
+                    best.launches = launches;
                     best.g = g;
                 }
             }
         }
     }
-    if (loaded >= 3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 * march + (in.wall_x ? 5.0 : 0.0)) best.nt = 0;
+    // x walls: an exchange (5 us) after every step of the marching kernel, after the last launch
+    // of windows
+    const double walls = in.wall_x ? 5.0 : 0.0;
+    if (loaded + walls >= double(n) * (3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 * march + walls)) best.nt = 0;
     return best;
 }
 

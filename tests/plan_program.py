@@ -38,12 +38,12 @@ int main() {
             in.nt[0] = kSmallWindow;
             in.nt[1] = large_window(in.qf, qs, in.prec, in.coll, nc);
             const BlockPlan p = block_plan(in, n);
-            std::printf("%d %d %d %d %d %d %d\n", p.nt, p.k, p.g.lw, p.g.hx, p.g.hz, p.g.tiles_x, p.g.tiles_z);
+            std::printf("%d %lld %d %d %d %d %d\n", p.nt, p.launches, p.g.lw, p.g.hx, p.g.hz, p.g.tiles_x, p.g.tiles_z);
         }
     }
 }
 """
-FIELDS = ("nt", "k", "lw", "hx", "hz", "tiles_x", "tiles_z")
+FIELDS = ("nt", "launches", "lw", "hx", "hz", "tiles_x", "tiles_z")
 PRECS = {"fp64": 0, "fp32": 1, "fp16": 2, "bf16": 3}
 TRT, VD, GK, MRT = 1, 2, 4, 8
 

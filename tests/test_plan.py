@@ -52,3 +52,26 @@ def test_steps_of_a_launch():
         assert n // m <= steps <= -(-n // m), (n, m, i, steps)
     for n, m in ((1, 1), (7, 3), (200, 7), (1000, 1000)):
         assert sum(plans.steps_of_launch([(n, m, i) for i in range(m)])) == n
+
+
+def test_windows_are_those_of_the_steps_that_run():
+    """The halo of a call's windows is the one that its longest launch needs, whatever the
+    number of steps, and an even call takes an even number of launches."""
+    rng = random.Random(5)
+    calls = [_call(512, 1, 200, "fp64", wall_x=True), _call(17, 33, 9), _call(200, 200, 6, "fp64"), _call(512, 512, 5)]
+    for _ in range(300):
+        nx, ny = (int(2 ** rng.uniform(0, 11)) for _ in range(2))
+        calls.append(_call(nx, ny, int(2 ** rng.uniform(0, 9)), rng.choice(list(plans.PRECS)), rng.choice((0, 9)),
+                           rng.choice((5, 9)), wall_x=rng.random() < 0.5))
+    ran = 0
+    for c, p in zip(calls, plans.windows(calls)):
+        if not p["nt"]:
+            continue
+        ran += 1
+        k = -(-c["n"] // p["launches"])
+        assert k <= 128 and (p["launches"] - c["n"]) % 2 == 0, (c, p)
+        halo = 2 * k - 1 if c["qf"] else k - 1
+        bw, bh = 1 << p["lw"], p["nt"] >> p["lw"]
+        assert p["hx"] == (0 if c["nx"] <= bw else halo), (c, p)
+        assert p["hz"] == (0 if c["ny"] <= bh else halo), (c, p)
+    assert ran > 200
