@@ -230,9 +230,11 @@ int lbm_init_multi(const lbm_config* cfg, void* state, size_t state_bytes, const
 
 /* Advance nsteps >= 0 time steps (Section 3: moments, forces, BGK collision of
  * f, g, h^A, h^B, streaming with periodic or bounce-back boundaries).  Kernel launches
- * only: the call may be recorded in a HIP graph.  An even number of steps leaves the state
- * in the population copy where it began, so such a graph may be replayed, between other
- * calls that take an even number of steps as well (lbm_step_count counts calls, not replays). */
+ * only: the call may be recorded in a HIP graph.  From the first recorded call on a handle
+ * (of any entry point) an even number of steps leaves the state in the population copy where
+ * it began, so a graph that takes an even number of steps, or none, may be replayed, between
+ * other calls that take an even number of steps as well (lbm_step_count counts calls, not
+ * replays). */
 int lbm_step(lbm_handle* h, int64_t nsteps, void* stream);
 
 /* Write the macroscopic fields of the current state into out[i] for each bit

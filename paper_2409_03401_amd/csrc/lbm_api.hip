@@ -353,6 +353,7 @@ struct lbm_handle {
     const double* muA0;
     const double* muB0;
     bool given_c;  // made by lbm_init_composition
+    bool recorded;  // a graph holds a call on copy[cur]
 };
 
 namespace {
@@ -485,6 +486,16 @@ int launched(const char* what) {
     return LBM_OK;
 }
 
+// Note a call on copy[cur] that is being recorded in a graph: from then on calls of an even
+// number of steps leave the state in the copy where it was, so that the replays, and the
+// calls between them, find it there
+void note_recording(lbm_handle* h, hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (h->recorded) return;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+    else if (status != hipStreamCaptureStatusNone) h->recorded = true;
+}
+
 // Windows of a 2D call of n steps (nt = 0: the marching kernel, which also takes the states
 // whose buoyancy needs the mean of every step)
 BlockPlan plan_call(const lbm_handle* h, int64_t n) {
@@ -494,7 +505,7 @@ BlockPlan plan_call(const lbm_handle* h, int64_t n) {
     const int coll = (c.collision == LBM_TRT ? COLL_TRT : c.collision == LBM_MRT ? COLL_MRT : 0) |
                      (c.variable_density ? COLL_VD : 0) | (c.general_kappa ? COLL_GK : 0);
     return block_plan(PlanInput{L.NX, L.NZ, L.qf, L.nslots, L.prec, double(L.copy_bytes), L.whole, h->base.wall_x != 0,
-                                coll, {h->ks->block_nt[0], h->ks->block_nt[1]}}, n);
+                                coll, {h->ks->block_nt[0], h->ks->block_nt[1]}, h->recorded}, n);
 }
 
 }  // namespace
@@ -562,8 +573,10 @@ int init_impl(const lbm_config* cfg, void* state, size_t state_bytes, const doub
     h->muA0 = muA0;
     h->muB0 = muB0;
     h->given_c = cA0 != nullptr;
+    h->recorded = false;
     fill_params(h);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    note_recording(h, s);
 
     auto bail = [&](int r) { delete h; return r; };
     {
@@ -640,6 +653,7 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps < 0");
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (nsteps == 0) return LBM_OK;
+    note_recording(h, s);
     KParams kp[2] = {h->base, h->base};
     set_slots(h, kp[0], h->copy[0], h->copy[1]);
     set_slots(h, kp[1], h->copy[1], h->copy[0]);
@@ -688,6 +702,7 @@ int lbm_moments(lbm_handle* h, uint32_t mask, void* const* out, int32_t out_dtyp
     for (int i = 0; i < LBM_NMOM; ++i)
         if ((mask >> i & 1u) && !out[i]) return fail(LBM_EINVAL, "NULL output for a requested moment");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    note_recording(h, s);
     KParams kp = h->base;
     set_slots(h, kp, h->copy[h->cur], nullptr);
     for (int i = 0; i < kNumMom; ++i) kp.mout[i] = nullptr;
@@ -787,6 +802,7 @@ int lbm_get_populations(lbm_handle* h, double* dst, void* stream) {
     if (!dst) return fail(LBM_EINVAL, "dst is NULL");
     KParams kp = h->base;
     set_slots(h, kp, h->copy[h->cur], nullptr);
+    note_recording(h, static_cast<hipStream_t>(stream));
     h->ks->get_pops(kp, h->L.nslots, h->L.nodes, dst, static_cast<hipStream_t>(stream));
     return launched("get_populations kernel");
 }
@@ -796,6 +812,7 @@ int lbm_set_populations(lbm_handle* h, const double* src, void* stream) {
     if (!src) return fail(LBM_EINVAL, "src is NULL");
     KParams kp = h->base;
     set_slots(h, kp, nullptr, h->copy[h->cur]);
+    note_recording(h, static_cast<hipStream_t>(stream));
     h->ks->set_pops(kp, h->L.nslots, h->L.nodes, src, static_cast<hipStream_t>(stream));
     return launched("set_populations kernel");
 }
@@ -821,6 +838,7 @@ int lbm_save(lbm_handle* h, void* dst, void* stream) {
     if (int r = check_handle(h)) return r;
     if (!dst) return fail(LBM_EINVAL, "dst is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    note_recording(h, s);
     LBM_HIP(hipMemcpyAsync(dst, h->copy[h->cur], h->L.copy_bytes, hipMemcpyDeviceToDevice, s));
     LBM_HIP(hipMemcpyAsync(static_cast<char*>(dst) + h->L.copy_bytes, h->aux, sizeof(double),
                            hipMemcpyDeviceToDevice, s));
@@ -831,6 +849,7 @@ int lbm_restore(lbm_handle* h, const void* src, void* stream) {
     if (int r = check_handle(h)) return r;
     if (!src) return fail(LBM_EINVAL, "src is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    note_recording(h, s);
     LBM_HIP(hipMemcpyAsync(h->copy[h->cur], src, h->L.copy_bytes, hipMemcpyDeviceToDevice, s));
     LBM_HIP(hipMemcpyAsync(h->aux, static_cast<const char*>(src) + h->L.copy_bytes, sizeof(double),
                            hipMemcpyDeviceToDevice, s));

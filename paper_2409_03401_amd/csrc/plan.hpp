@@ -70,6 +70,7 @@ struct PlanInput {
     bool wall_x;
     int coll;              // flags of Coll
     int nt[2];             // threads of the small and the large window
+    bool keep_copy;        // the state ends in the copy where single steps would leave it
 };
 
 // windows of nt nodes, 2^lw wide, for up to k steps per launch; false: the halo leaves none
@@ -95,12 +96,11 @@ constexpr long long steps_of_launch(long long n, long long launches, long long i
     return n / launches + (i < n % launches ? 1 : 0);
 }
 
-// launches of a call of n steps with at most k steps each: an even number for an even number
-// of steps, so that the state ends in the copy where it began, as with one step per launch
-// (a call recorded in a graph goes on from its own result when replayed)
-constexpr long long launches_of(long long n, int k) {
+// launches of a call of n steps with at most k steps each.  keep_copy: an even number for an
+// even number of steps and an odd one for an odd number, as with one step per launch
+constexpr long long launches_of(long long n, int k, bool keep_copy) {
     const long long l = (n + k - 1) / k;
-    return l + ((l ^ n) & 1);
+    return l + (keep_copy ? (l ^ n) & 1 : 0);
 }
 
 struct BlockPlan {
@@ -148,7 +148,7 @@ inline BlockPlan block_plan(const PlanInput& in, long long n) {
     // the longest launch of every way to share the steps among fewer launches
     int longest[128], ways = 0;
     for (int k = int(std::min(n, 128LL)); k > 0; --k) {
-        const long long launches = launches_of(n, k);
+        const long long launches = launches_of(n, k, in.keep_copy);
         k = int((n + launches - 1) / launches);
         longest[ways++] = k;
     }
@@ -160,7 +160,7 @@ inline BlockPlan block_plan(const PlanInput& in, long long n) {
                 if (!block_geometry(in, nt, lw, longest[i], g)) break;
                 const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
                 if (windows * nt > double(kMaxThreads)) break;  // more with every further step
-                const long long launches = launches_of(n, longest[i]);
+                const long long launches = launches_of(n, longest[i], in.keep_copy);
                 const double k = double(n) / double(launches);
                 const double mem = bytes * 1024.0 / rate *
                                    (1.0 + 16.5 / ((1 << lw) * word) + share * (1.0 + 44.0 / (g.ix * word)));

@@ -17,7 +17,7 @@ int main() {
     long long n, cols, nz;
     PlanInput in{};
     char what;
-    int qs, nc, whole, wall_x;
+    int qs, nc, whole, wall_x, keep_copy;
     while (std::scanf(" %c", &what) == 1) {
         if (what == 'f') {  // chunk of the 3D kernels without the stencil
             if (std::scanf("%lld %lld", &cols, &nz) != 2) return 1;
@@ -30,11 +30,12 @@ int main() {
             if (std::scanf("%lld %lld %lld", &n, &cols, &nz) != 3) return 1;
             std::printf("%lld\n", steps_of_launch(n, cols, nz));
         } else {  // windows of a 2D call
-            if (std::scanf("%d %d %d %d %d %d %lf %d %d %d %lld", &in.nx, &in.nz, &in.qf, &qs, &nc, &in.prec,
-                           &in.copy_bytes, &whole, &wall_x, &in.coll, &n) != 11) return 1;
+            if (std::scanf("%d %d %d %d %d %d %lf %d %d %d %d %lld", &in.nx, &in.nz, &in.qf, &qs, &nc, &in.prec,
+                           &in.copy_bytes, &whole, &wall_x, &in.coll, &keep_copy, &n) != 12) return 1;
             in.nslots = in.qf + (1 + nc) * qs;
             in.whole = whole != 0;
             in.wall_x = wall_x != 0;
+            in.keep_copy = keep_copy != 0;
             in.nt[0] = kSmallWindow;
             in.nt[1] = large_window(in.qf, qs, in.prec, in.coll, nc);
             const BlockPlan p = block_plan(in, n);
@@ -87,7 +88,8 @@ def steps_of_launch(launches):
 
 
 def windows(calls):
-    """Windows of every call: dicts with nx, ny, qf, qs, nc, prec, wall_x, coll, n."""
+    """Windows of every call: dicts with nx, ny, qf, qs, nc, prec, wall_x, coll, n, and keep_copy
+    for a state of which a graph holds a call."""
     lines = []
     for c in calls:
         prec, nodes = PRECS[c["prec"]], c["nx"] * c["ny"]
@@ -100,5 +102,5 @@ def windows(calls):
         copy = moving * slot(word) + rest * slot(max(word, 4))
         whole = int(c["nx"] * word % 128 == 0)
         lines.append(f"w {c['nx']} {c['ny']} {c['qf']} {c['qs']} {c['nc']} {prec} {copy} {whole} "
-                     f"{int(c['wall_x'])} {c['coll']} {c['n']}")
+                     f"{int(c['wall_x'])} {c['coll']} {int(c.get('keep_copy', False))} {c['n']}")
     return [dict(zip(FIELDS, r)) for r in _ask(lines)]

@@ -11,8 +11,8 @@ pytestmark = pytest.mark.skipif(not plans.available(), reason="no C++ compiler")
 MAX_THREADS = 2**32 - 1  # of a launch along one axis of its grid
 
 
-def _call(nx, ny, n, prec="fp32", qf=0, qs=5, nc=2, wall_x=False, coll=0):
-    return dict(nx=nx, ny=ny, n=n, prec=prec, qf=qf, qs=qs, nc=nc, wall_x=wall_x, coll=coll)
+def _call(nx, ny, n, prec="fp32", qf=0, qs=5, nc=2, wall_x=False, coll=0, keep_copy=False):
+    return dict(nx=nx, ny=ny, n=n, prec=prec, qf=qf, qs=qs, nc=nc, wall_x=wall_x, coll=coll, keep_copy=keep_copy)
 
 
 def test_flat_chunks_fit_a_launch():
@@ -56,22 +56,30 @@ def test_steps_of_a_launch():
 
 def test_windows_are_those_of_the_steps_that_run():
     """The halo of a call's windows is the one that its longest launch needs, whatever the
-    number of steps, and an even call takes an even number of launches."""
+    number of steps, and with a recorded graph an even call takes an even number of launches."""
     rng = random.Random(5)
     calls = [_call(512, 1, 200, "fp64", wall_x=True), _call(17, 33, 9), _call(200, 200, 6, "fp64"), _call(512, 512, 5)]
     for _ in range(300):
         nx, ny = (int(2 ** rng.uniform(0, 11)) for _ in range(2))
         calls.append(_call(nx, ny, int(2 ** rng.uniform(0, 9)), rng.choice(list(plans.PRECS)), rng.choice((0, 9)),
-                           rng.choice((5, 9)), wall_x=rng.random() < 0.5))
+                           rng.choice((5, 9)), wall_x=rng.random() < 0.5, keep_copy=rng.random() < 0.5))
     ran = 0
     for c, p in zip(calls, plans.windows(calls)):
         if not p["nt"]:
             continue
         ran += 1
         k = -(-c["n"] // p["launches"])
-        assert k <= 128 and (p["launches"] - c["n"]) % 2 == 0, (c, p)
+        assert k <= 128 and (not c["keep_copy"] or (p["launches"] - c["n"]) % 2 == 0), (c, p)
         halo = 2 * k - 1 if c["qf"] else k - 1
         bw, bh = 1 << p["lw"], p["nt"] >> p["lw"]
         assert p["hx"] == (0 if c["nx"] <= bw else halo), (c, p)
         assert p["hz"] == (0 if c["ny"] <= bh else halo), (c, p)
     assert ran > 200
+
+
+def test_launches_are_even_for_graphs_only():
+    """Two steps of a large box without flow take one launch of windows; two of one step each,
+    which move as many bytes as single steps, only where a graph holds a call."""
+    for p, launches in zip(plans.windows([_call(1500, 1300, 2, keep_copy=k) for k in (False, True)]), (1, 2)):
+        assert p["nt"] == 0 or p["launches"] == launches, p
+    assert plans.windows([_call(1500, 1300, 2)])[0]["launches"] == 1
