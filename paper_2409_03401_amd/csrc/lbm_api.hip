@@ -109,12 +109,8 @@ Tiles make_tiles(const Layout& L, int tx, int ty) {
     t.ty = ty;
     t.gx = (L.NX + tx - 1) / tx;
     t.gy = (L.NY + ty - 1) / ty;
-    const long long cols = std::max(1LL, (long long)t.gx * t.gy);
-    long long nchunks;
     if (L.dim == 2) {
-        // rows of TX nodes: about 2048 work-groups (8 per compute unit); a 512^2 box then
-        // takes one or two rows per group, the fastest on one MI355X (measured)
-        nchunks = 2048 / cols;
+        t.zc = row_chunk(L.NX, L.NZ, tx);
     } else {
         // 3D columns: measured on one MI355X (256 compute units), the step is fastest when
         // all of its work-groups are resident at once, with two per compute unit for
@@ -124,11 +120,12 @@ Tiles make_tiles(const Layout& L, int tx, int ty) {
         // GLUPS against 20.0 with 256-plane chunks).  Equal chunks: zc divides nz evenly
         // when it can.  The layout depends only on the configuration, never on the device.
         constexpr long long kCUs = 256;
+        const long long cols = std::max(1LL, (long long)t.gx * t.gy);
         const long long per_cu = (L.prec == LBM_FP32 || L.prec == LBM_FP64) ? 2 : 3;
-        nchunks = cols <= per_cu * kCUs ? (per_cu * kCUs) / cols : (L.NZ + 63) / 64;
+        long long nchunks = cols <= per_cu * kCUs ? (per_cu * kCUs) / cols : (L.NZ + 63) / 64;
+        nchunks = std::max(1LL, std::min<long long>(L.NZ, nchunks));
+        t.zc = int((L.NZ + nchunks - 1) / nchunks);
     }
-    nchunks = std::max(1LL, std::min<long long>(L.NZ, nchunks));
-    t.zc = int((L.NZ + nchunks - 1) / nchunks);
     if (const char* e = std::getenv("LBM_ZC")) {
         const int v = std::atoi(e);
         if (v > 0) t.zc = std::min(v, L.NZ);

@@ -61,6 +61,14 @@ constexpr int large_window(int qf, int qs, int prec, int coll, int nc) {
     return (qf > 0 && regs <= most && window_lds(qf, qs, prec, nc, 1024) <= 160 * 1024) ? 1024 : 512;
 }
 
+// rows of a marching work-group in 2D, whose columns are `threads` nodes wide: about 2048
+// work-groups (8 per compute unit); a 512^2 box then takes one or two rows per group, the
+// fastest on one MI355X (measured)
+constexpr int row_chunk(int nx, int nz, int threads) {
+    const int cols = (nx + threads - 1) / threads, groups = std::max(1, std::min(nz, 2048 / cols));
+    return (nz + groups - 1) / groups;
+}
+
 // what the plan of a 2D call depends on
 struct PlanInput {
     int nx, nz;            // kernel frame
@@ -109,85 +117,142 @@ struct BlockPlan {
     BlockGeom g;
 };
 
-// How a call of n steps is cut into windows: the estimate of its time in us, smallest over
-// the windows of both sizes (256 and 512 or 1024 nodes) of every power-of-two width and the
-// numbers of launches that the call can take with up to 128 steps each.  The windows are those
-// of the steps that are run, ceil(n / launches).  A launch takes 4 us, each step its barriers
-// (0.36 us, 0.68 with flow), and a window its loads, collisions and stores: alone on a
-// compute unit the latency of these, else their throughput.  The windows of all 256 units
-// share the memory (`mem`, with the part of a 128-byte line that a row's ends waste, and
-// less while both copies stay in the last-level cache); the collisions, `cmp`, overlap with
-// it where several windows share a unit.  One window of 1024 nodes has a unit to itself, so
-// these run in whole rounds; one of 512 FP64 nodes with flow leaves part of a unit idle.
-// The constants are a fit to 1900 timings (ten families, 64^2 to 2047^2): the choice is
-// within 0.8 % of the fastest on average (6 % with a fit to fewer: 150 x 93 D2Q9 + 3 x D2Q5
-// FP32 closed 3.01 us a step, 2.71 now; 2047^2 D2Q9 BF16 68.1, 59.2 now; 512^2 D2Q9 + 3 x
-// D2Q5 FP64 18.5, 15.9 now).  The marching kernel stays where its own estimate is lower.
+// us that the chip takes for the collisions of 2^18 nodes, a factor of the model and one of the
+// storage format: [model][scalar lattice of 5 or 9 directions][with flow], [with flow][precision]
+constexpr double collision_time(int qf, int nslots, int coll, int prec) {
+    constexpr double model[7][2][2] = {
+        {{0.618, 1.11}, {0.965, 1.7}},     // BGK
+        {{0.759, 1.71}, {1.22, 2.32}},     // TRT
+        {{0.898, 1.88}, {1.83, 3.1}},      // MRT
+        {{0.0, 1.36}, {0.0, 1.94}},        // variable density
+        {{0.0, 1.98}, {0.0, 2.61}},        // variable density, TRT
+        {{0.98, 1.72}, {1.33, 2.15}},      // general curvatures
+        {{0.796, 1.38}, {0.0, 0.0}},       // three compositions
+    };
+    constexpr double store[2][4] = {{1.46, 1.1, 1.6, 1.3}, {1.37, 0.975, 1.44, 1.23}};
+    const int flow = qf > 0 ? 1 : 0, ns = nslots - qf;
+    const int m = ns == 20 ? 6 : (coll & COLL_GK) ? 5 : (coll & COLL_MRT) ? 2
+                : (coll & COLL_VD) ? ((coll & COLL_TRT) ? 4 : 3) : (coll & COLL_TRT) ? 1 : 0;
+    return model[m][ns == 27 ? 1 : 0][flow] * store[flow][prec];
+}
+
+// waves that a SIMD holds for kernels of v vector registers
+constexpr int waves_of(double v) { return std::max(1, std::min(8, 512 / ((int(v) + 7) / 8 * 8))); }
+
+// share of the `traffic` of a step, in bytes, that stays in the last-level cache
+inline double cached(double traffic, double size) {
+    const double r = traffic / size, r2 = r * r;
+    return 1.0 / (1.0 + r2 * r2);
+}
+
+// us of one step with the marching kernel, `work` from collision_time: the latency of a
+// work-group's rows (with flow two more than it updates), in rounds of the groups that are
+// resident (about as many registers as the kernels have, and the LDS ring of scalar
+// populations), or the time of the bytes (rows of whole lines take non-temporal stores) and of
+// the collisions
+inline double march_time(const PlanInput& in, int qs, int nc, double work) {
+    const bool flow = in.qf > 0, wide = (in.coll & (COLL_MRT | COLL_GK)) != 0, s16 = in.prec == P16 || in.prec == PB16;
+    const int ns = in.nslots;
+    int resident = waves_of(!flow ? (in.prec == P64 ? 32 + 2.8 * ns : 38 + 1.5 * ns + (wide ? 20 : 0))
+                            : in.prec == P64 ? 6.5 * ns - 10 + (wide ? 25 : 0)
+                            : s16 ? 90 + ns + (wide ? 15 : 0) : 40 + 2.6 * ns + (wide ? 12 : 0));
+    if (flow) {
+        const int word = in.prec == P64 ? 8 : 4;
+        const int ring = 2 * 256 * word * (1 + nc) * (s16 ? 1 + (qs - 1) / 2 : qs);
+        if (ring <= 96 * 1024) resident = std::min(resident, 160 * 1024 / (ring + 3 * 258 * word));
+    }
+    const int zc = row_chunk(in.nx, in.nz, 256), cols = (in.nx + 255) / 256;
+    const double x = double(cols) * ((in.nz + zc - 1) / zc) / 256.0 / resident;
+    const double rounds = x <= 1.0 ? 1.0 : 0.89 * std::ceil(x) + 0.11 * x;
+    const double fill = flow ? 2.0 / zc : 0.0;  // rows read besides those updated
+    const double traffic = 2.0 * in.copy_bytes, hit = cached(traffic, 311e6);
+    const double mem = traffic * (in.whole ? hit / 5.92e6 + (1.0 - hit) / 5.52e6 : hit / 7.63e6 + (1.0 - hit) / 4.49e6);
+    const double lanes = 256.0 * cols / in.nx;  // of a row's work-groups, over its nodes
+    const double cmp = 0.583 * work * double(in.nx) * in.nz / 262144.0 * lanes * lanes * lanes;
+    const double busy = mem * (1.0 + 0.167 * fill) + cmp * (1.0 + 0.057 * fill);
+    const double alone = rounds * (zc + (flow ? 2 : 0)) * (1.31 + 0.442 * work);
+    return 2.09 + std::sqrt(alone * alone + busy * busy);
+}
+
+// windows of nt nodes that a compute unit holds, by LDS and about as many registers as the
+// kernels have
+constexpr int resident_windows(const PlanInput& in, int qs, int nc, int nt) {
+    const bool flow = in.qf > 0, s16 = in.prec == P16 || in.prec == PB16;
+    double v = in.prec == P64 ? 26 + 4.4 * in.nslots + (flow ? 20 : 0)
+                              : 28 + 2.4 * in.nslots + (flow ? 14 : 0) + (s16 ? 4 : 0);
+    if (flow && (in.coll & (COLL_MRT | COLL_GK)) != 0) v += 12;
+    if (flow && s16 && qs == 9 && (in.coll & (COLL_TRT | COLL_MRT)) != 0) v += 24;
+    return std::max(1, std::min(std::min(160 * 1024 / window_lds(in.qf, qs, in.prec, nc, nt), 2048 / nt),
+                                waves_of(v) * 256 / nt));
+}
+
+// us of one launch of windows of nt nodes, `resident` of them on a unit, k steps each; `mem`: us
+// that the chip takes for the bytes of a copy of 2^18 nodes.  A launch takes 4 us, and a round of
+// resident windows the latency of its steps' collisions and barriers and the throughput of its
+// loads and stores, which share the memory (a row's ends waste parts of 128-byte lines), and of
+// its collisions.  Windows of one unit overlap the two; a window that has the unit to itself
+// hardly, and its rounds are whole.
+inline double window_time(const PlanInput& in, const BlockGeom& g, int nt, int resident, double k, double work, double mem) {
+    const double nodes = double(in.nx) * in.nz, bytes = in.copy_bytes / nodes, word = bytes / in.nslots;
+    const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
+    // 1024 nodes with TRT on the D2Q9 lattices spill 33 registers (512^2 BF16: 20 us a step,
+    // 15.5 with the marching kernel)
+    if (nt == 1024 && (in.coll & COLL_TRT) != 0 && word < 3.5 && in.nslots > 30) work *= 1.57;
+    const double move = mem * (1.0 + share * (1.0 + 57.5 / (g.ix * word))), collide = k * work;
+    const double busy = (std::max(move, collide) + (resident == 1 ? 0.65 : 0.48) * std::min(move, collide)) *
+                        (resident == 1 && nt == 512 && windows > 256.0 ? 1.22 : 1.0);
+    const double x = windows / 256.0, held = std::min(std::ceil(x), double(resident));
+    const double r = x / resident, rounds = r <= 1.0 ? 1.0 : resident == 1 ? std::ceil(r) : 0.41 * std::ceil(r) + 0.59 * r;
+    const double load = nt == 1024 ? 0.0146 * bytes : 0.0;  // nothing else runs while the one window loads
+    return (in.qf ? 3.72 : 3.13) + rounds * (load + (in.qf ? 0.208 * k : 0.0) + 0.353 * collide + held * nt / 1024.0 * busy);
+}
+
+// How a call of n steps is cut into windows: the smallest estimate of its time over the
+// windows of both sizes and every power-of-two width and over the numbers of launches that the
+// call can take with up to 128 steps each (the windows are those of the steps that run,
+// ceil(n / launches)).  The marching kernel stays unless that is below its own estimate by
+// what the two may err.  The constants above are a fit to 27 000 timings (22 families in four
+// precisions, 256 x 1 to 3001 x 1111 nodes, windows of 1 to 16 steps): windows within 7 % (rms),
+// the marching kernel within 9 %.  Over calls of 1 to 40 steps on these grids the plan takes
+// 1.7 % longer than the best choice on average, and in one call of 90 over 2 % longer than the
+// marching kernel (an estimate that knew nothing of the models' collisions: 4.9 %, one of 25,
+// the worst MRT on D2Q9 FP16 without flow, 512^2 in 10 steps, 139 us against 87).
 inline BlockPlan block_plan(const PlanInput& in, long long n) {
     BlockPlan best;
-    const double nodes = double(in.nx) * in.nz, flow = in.qf ? 1.0 : 0.0;
-    const double bytes = in.copy_bytes / nodes;  // of a node's populations
-    const double word = bytes / in.nslots;
-    const double cmp = 0.0067 * in.nslots * (13.0 + 14.4 * flow);  // of 1024 nodes, one step
-    const double rate = 2.0 * bytes * nodes > 124e6 ? 33.7e3 : 47e3;  // bytes/us of one unit
-    // the marching kernel's time, and how much longer than the estimate the best windows take
-    // (`heavy`): with flow the collisions of the less usual models and the conversions of
-    // 16-bit storage count, most for boxes beyond the last-level cache (2048^2 D2Q9 + 3 x D2Q5,
-    // march / windows: BF16 112 / 109 us, FP16 116 / 128, BF16 with TRT 116 / 131; 1500^2, whose
-    // rows are not whole lines, BF16 74 / 52)
-    const bool s16 = word < 3.5, trt = (in.coll & COLL_TRT) != 0;
-    const bool wide = (in.coll & (COLL_MRT | COLL_GK)) != 0;
-    double heavy = 1.0, march = in.whole ? 1.0 : (s16 ? 1.25 : 1.1);
-    if (flow > 0.0 && s16) {
-        heavy = (in.prec == P16 ? 1.39 : 1.2) * (wide ? 1.3 : trt ? 1.15 : 1.0) *
-                ((in.coll & COLL_VD) != 0 ? 1.125 : 1.0);
-        march *= wide ? 1.23 : 1.12;
-    } else if (flow > 0.0 && word > 6.0 && wide) {
-        heavy = 1.28;  // 2048^2 D2Q9 + 3 x D2Q5 FP64, MRT: 344 / 363 us
-    }
-    // the longest launch of every way to share the steps among fewer launches
+    const double work = collision_time(in.qf, in.nslots, in.coll, in.prec);
+    const int qs = (in.nslots - in.qf) % 9 == 0 ? 9 : 5, nc = (in.nslots - in.qf) / qs - 1;
+    // the ways to share the steps among launches: their number and the longest of them
+    long long launches[128];
     int longest[128], ways = 0;
     for (int k = int(std::min(n, 128LL)); k > 0; --k) {
-        const long long launches = launches_of(n, k, in.keep_copy);
-        k = int((n + launches - 1) / launches);
-        longest[ways++] = k;
+        launches[ways] = launches_of(n, k, in.keep_copy);
+        k = longest[ways] = int((n + launches[ways] - 1) / launches[ways]);
+        ++ways;
     }
-    double cost = 1e30, loaded = 1e30;  // of the call
+    // x walls: an exchange (5 us) after every step of the marching kernel, after the last launch
+    // of windows
+    const double walls = in.wall_x ? 5.0 : 0.0;
+    double cost = double(n) * (march_time(in, qs, nc, work) + walls);  // of the call
+    const double hit = cached(2.0 * in.copy_bytes, 296e6);
+    const double mem = in.copy_bytes / (double(in.nx) * in.nz) * 1024.0 * (hit / 49.6e3 + (1.0 - hit) / 31.3e3);
     for (int nt : in.nt) {
+        const int resident = resident_windows(in, qs, nc, nt);
         for (int lw = 4; (1 << lw) <= nt; ++lw) {
             for (int i = ways - 1; i >= 0; --i) {
                 BlockGeom g;
                 if (!block_geometry(in, nt, lw, longest[i], g)) break;
-                const double windows = double(g.tiles_x) * g.tiles_z, share = std::min(1.0, nodes / (windows * nt));
-                if (windows * nt > double(kMaxThreads)) break;  // more with every further step
-                const long long launches = launches_of(n, longest[i], in.keep_copy);
-                const double k = double(n) / double(launches);
-                const double mem = bytes * 1024.0 / rate *
-                                   (1.0 + 16.5 / ((1 << lw) * word) + share * (1.0 + 44.0 / (g.ix * word)));
-                const double alone = nt / 1024.0 * (0.44 + 0.456 * k * cmp);
-                double rounds = windows * nt / (256.0 * 1024.0);
-                if (nt == 1024 && rounds > 1.0) rounds = std::ceil(rounds);
-                if (nt > 256 && flow > 0.0 && word > 6.0) rounds *= 1.43;
-                // 1024 nodes with TRT on the D2Q9 lattices spill 33 registers (512^2 BF16: 20 us
-                // a step, 15.5 with the marching kernel)
-                const double spill = trt && s16 && in.nslots > 30 && nt == 1024 ? 1.9 : 1.0;
-                const double busy = rounds * spill * (mem + (0.395 - 0.087 * flow) * k * cmp);
-                const double base = 3.95 + (0.364 + 0.314 * flow) * k;
-                const double t = double(launches) * (base + std::max(alone, busy));
+                if (double(g.tiles_x) * g.tiles_z * nt > double(kMaxThreads)) break;  // more with every further step
+                const double margin = longest[i] == 1 ? 0.88 : 0.95, calls = double(launches[i]);
+                const double t = (calls * window_time(in, g, nt, resident, double(n) / calls, work, mem) + walls) / margin;
                 if (t < cost) {
                     cost = t;
-                    loaded = double(launches) * (base + std::max(alone, busy * heavy));
                     best.nt = nt;
-                    best.launches = launches;
+                    best.launches = launches[i];
                     best.g = g;
                 }
             }
         }
     }
-    // x walls: an exchange (5 us) after every step of the marching kernel, after the last launch
-    // of windows
-    const double walls = in.wall_x ? 5.0 : 0.0;
-    if (loaded + walls >= double(n) * (3.6 + 3.5 * flow + 2.0 * bytes * nodes / 4.85e6 * march + walls)) best.nt = 0;
     return best;
 }
 

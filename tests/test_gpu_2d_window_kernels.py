@@ -1,6 +1,6 @@
 """The window kernels of every 2D family against one step per launch, bit for bit, with the
 window that runs stated: the plan of each call is evaluated on the host (csrc/plan.hpp) and
-has to take the small window on one grid and the family's large window on the other.  Both
+has to take the small window on one grid and the family's large window on another.  The
 grids are ragged, larger than the window and take several launches a call."""
 
 import numpy as np
@@ -32,14 +32,14 @@ STEPS = 20
 
 
 def _large(model, scalar, flow, prec):
-    """Threads of the large window where the plan takes it on the larger grid: without flow
-    512, with flow 1024 (512 on D2Q9 with MRT or general curvatures).  FP64 with flow, and TRT
-    with flow on D2Q9 in 16-bit storage, take the small one."""
-    if not flow:
+    """Threads of the family's large window (csrc/plan.hpp: large_window)."""
+    if not flow or prec == "fp64" or (model in ("mrt", "kappa") and scalar == "D2Q9"):
         return 512
-    if prec == "fp64" or ("trt" in model and scalar == "D2Q9" and prec in ("fp16", "bf16")):
-        return 256
-    return 512 if model in ("mrt", "kappa") and scalar == "D2Q9" else 1024
+    return 1024
+
+
+# ragged grids: the first on which the plan takes the large window
+LARGE = [(300, 257), (130, 97), (200, 131), (517, 300), (600, 41), (350, 200), (1100, 163)]
 
 
 @pytest.mark.parametrize("prec", sorted(plans.PRECS))
@@ -49,9 +49,14 @@ def test_windows(model, scalar, flow, prec):
         pytest.skip("no GPU")
     from paper_2409_03401_amd.lbm import Simulation
     kw, coll = MODELS[model]
-    for nx, ny, bc, nt in ((75, 50, (W, W, P), 256), (300, 257, (P, W, P), _large(model, scalar, flow, prec))):
-        plan = plans.windows([dict(nx=nx, ny=ny, n=STEPS, prec=prec, qf=9 if flow else 0, qs=int(scalar[3:]),
-                                   nc=3 if model == "three" else 2, wall_x=bc[0] == W, coll=coll)])[0]
+
+    def plan_of(nx, ny, wall_x):
+        return plans.windows([dict(nx=nx, ny=ny, n=STEPS, prec=prec, qf=9 if flow else 0, qs=int(scalar[3:]),
+                                   nc=3 if model == "three" else 2, wall_x=wall_x, coll=coll)])[0]
+    large = _large(model, scalar, flow, prec)
+    grid = next(g for g in LARGE if plan_of(*g, False)["nt"] == large)
+    for nx, ny, bc, nt in ((75, 50, (W, W, P), 256), (*grid, (P, W, P), large)):
+        plan = plan_of(nx, ny, bc[0] == W)
         assert plan["nt"] == nt and plan["launches"] >= 2, plan
         p = inputs._base(nx, ny, 1, bc=bc, M_A=(0.1, 0.07), M_B=(0.06, 0.09))
         p.update(FLOW if flow else {}, scalar=scalar)

@@ -83,3 +83,30 @@ def test_launches_are_even_for_graphs_only():
     for p, launches in zip(plans.windows([_call(1500, 1300, 2, keep_copy=k) for k in (False, True)]), (1, 2)):
         assert p["nt"] == 0 or p["launches"] == launches, p
     assert plans.windows([_call(1500, 1300, 2)])[0]["launches"] == 1
+
+
+# Calls whose marching kernel and windows differ by 15 % and more: grid, steps, precision, fluid
+# and scalar directions, model, what is allowed (steps a launch; 1: the marching kernel too), and
+# us measured for that and for a plan that knew nothing of the models' collisions
+MEASURED = [
+    (512, 512, 10, "fp16", 0, 9, plans.MRT, (1, 2), 87, 139),
+    (256, 128, 6, "fp64", 0, 9, plans.MRT, (3,), 21, 38),
+    (300, 257, 6, "fp16", 0, 9, plans.TRT, (3,), 19, 30),
+    (512, 256, 6, "fp32", 0, 5, plans.GK, (3,), 18, 28),
+    (1100, 1063, 10, "fp32", 0, 5, plans.GK, (2,), 146, 217),
+    (2048, 2048, 1, "fp32", 9, 5, plans.TRT, (1,), 167, 219),
+    (2048, 2048, 1, "fp32", 9, 5, plans.VD | plans.TRT, (1,), 168, 222),
+    # windows that a cautious plan would miss
+    (1024, 1024, 40, "fp32", 0, 5, 0, (3, 4, 5), 430, 1060),
+    (512, 512, 40, "fp32", 9, 5, 0, (2, 3), 357, 600),
+    (150, 93, 100, "fp32", 9, 5, 0, (2, 3, 6), 270, 1490),
+]
+
+
+@pytest.mark.parametrize("nx, ny, n, prec, qf, qs, coll, steps, us, us_other", MEASURED)
+def test_plans_where_the_kernels_differ(nx, ny, n, prec, qf, qs, coll, steps, us, us_other):
+    p = plans.windows([_call(nx, ny, n, prec, qf, qs, coll=coll)])[0]
+    taken = -(-n // p["launches"]) if p["nt"] else 1
+    assert taken in steps, p
+    if n == 1:
+        assert p["nt"] == 0, p
