@@ -311,8 +311,8 @@ int check_config(const lbm_config* c, Layout* L) {
     L->zc_flat = L->dim == 2 || L->tuned ? 0 : flat_chunk((long long)L->line.gx * L->line.gy, L->NZ, L->ks->nt);
     // The general kernel where its plain stores or its tiles are worth its registers: rows
     // that are not whole lines (87 x 123 x 70 FP64, D3Q19 scalars 276 us a step against 338),
-    // and whole rows of a width that 64 does not divide, in 3D
-    L->gen_steps = !L->whole || (L->dim == 3 && L->NX % kTileX != 0) || L->tuned;
+    // and in 3D whole rows that fill 64-wide tiles badly
+    L->gen_steps = !L->whole || (L->dim == 3 && general_tiles(L->NX, L->nodes, L->prec, L->qf, L->qs)) || L->tuned;
     L->nparts = std::max(L->line.groups(), L->gen.groups());
     // aux: kAuxHead doubles of scalars, then per-work-group partials (8 per group
     // of the fused kernel, 9 with a third composition; one per group of the Euler

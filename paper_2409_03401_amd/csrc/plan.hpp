@@ -24,6 +24,21 @@ constexpr bool tile_fits(int w, int h) {
            (w + 2) * (h + 2) <= kTileCells && 2 * (w + 2) + 2 * h <= kTileNodes;
 }
 
+// lanes of the 64-wide tiles of a row, over its nodes
+constexpr double tile_lanes(int nx) { return 64.0 * ((nx + 63) / 64) / nx; }
+// Steps of a 3D box whose rows are whole lines, but not of 64-wide tiles: the general kernel
+// where 64-wide tiles waste a sixth of their lanes and more, else its plain stores cost more than
+// the lanes (us a step, general / 64 x 4, D3Q7 with flow FP64: 80^3 80 / 91, 160^3 582 / 592,
+// 224 x 128 x 128 537 / 505; D3Q7 FP64 without flow 80^3 28 / 39, 224 x 128 x 128 251 / 246).  FP32 with flow gains
+// only on boxes that the last-level cache holds in good part (96^3 59 / 71, 96 x 200 x 150 215 /
+// 209, 160 x 96 x 80 95 / 90), and on D3Q19 scalars where half the lanes idle (32 x 128 x 128
+// 79 / 89, 96^3 150 / 143, 160^3 675 / 619)
+constexpr bool general_tiles(int nx, long long nodes, int prec, int qf, int qs) {
+    const double lanes = tile_lanes(nx);
+    if (qf > 0 && prec == P32) return qs == 19 ? lanes >= 1.5 : lanes > 1.2 && nodes < (3 << 19);
+    return lanes >= 1.2;
+}
+
 // planes per work-group of the 3D kernels without the phi stencil, for `cols` columns of
 // tiles: one, two on large grids (96^3 FP64 step 67.2 -> 61.2 us, 256^3 FP32 580 -> 550 us
 // against the chunks of the other kernels); 0, those chunks, where the launch would be too

@@ -26,6 +26,10 @@ int main() {
             int w, h;
             if (std::scanf("%d %d", &w, &h) != 2) return 1;
             std::printf("%d\n", int(tile_fits(w, h)));
+        } else if (what == 'g') {  // 3D steps of whole rows: the general kernel?
+            int nx, prec, qf;
+            if (std::scanf("%d %lld %d %d %d", &nx, &n, &prec, &qf, &qs) != 5) return 1;
+            std::printf("%d\n", int(general_tiles(nx, n, prec, qf, qs)));
         } else if (what == 'n') {  // steps of a launch
             if (std::scanf("%lld %lld %lld", &n, &cols, &nz) != 3) return 1;
             std::printf("%lld\n", steps_of_launch(n, cols, nz));
@@ -80,6 +84,13 @@ def flat_chunks(grids):
 def tile_fits(tiles):
     """Whether a 3D work-group can take every (width, height)."""
     return [bool(r[0]) for r in _ask([f"t {w} {h}" for w, h in tiles])]
+
+
+def general_tiles(boxes):
+    """Whether the steps of every (nx, ny, nz, precision, fluid, scalar directions), rows of whole
+    lines, go through the general kernel."""
+    return [bool(r[0]) for r in _ask([f"g {nx} {nx * ny * nz} {PRECS[prec]} {qf} {qs}"
+                                      for nx, ny, nz, prec, qf, qs in boxes])]
 
 
 def steps_of_launch(launches):

@@ -110,3 +110,22 @@ def test_plans_where_the_kernels_differ(nx, ny, n, prec, qf, qs, coll, steps, us
     assert taken in steps, p
     if n == 1:
         assert p["nt"] == 0, p
+
+
+def test_general_kernel_on_whole_rows():
+    """Boxes whose rows are whole lines, with us a step measured for the general kernel and for
+    64 x 4 tiles."""
+    measured = [
+        ((80, 80, 80, "fp64", 19, 7), 80, 91), ((160, 160, 160, "fp64", 19, 7), 582, 592),
+        ((224, 128, 128, "fp64", 19, 7), 537, 505), ((288, 96, 64, "fp64", 19, 7), 268, 247),
+        ((112, 112, 112, "fp64", 19, 19), 446, 435), ((224, 128, 128, "fp64", 19, 19), 1185, 1055),
+        ((80, 80, 80, "fp64", 19, 19), 178, 192), ((96, 200, 150, "fp64", 19, 19), 832, 916),
+        ((96, 96, 96, "fp32", 19, 7), 59, 71), ((160, 96, 80, "fp32", 19, 7), 95, 90),
+        ((224, 128, 128, "fp32", 19, 7), 300, 264), ((96, 200, 150, "fp32", 19, 7), 214, 209),
+        ((32, 128, 128, "fp32", 19, 19), 79, 89), ((96, 96, 96, "fp32", 19, 19), 150, 143),
+        ((160, 160, 160, "fp32", 19, 19), 674, 619), ((224, 128, 128, "fp32", 19, 19), 647, 530),
+        ((96, 96, 96, "fp32", 0, 7), 24, 32), ((224, 128, 128, "fp64", 0, 7), 251, 246),
+        ((64, 64, 64, "fp32", 19, 7), 2, 1), ((256, 256, 256, "bf16", 19, 7), 2, 1),
+    ]
+    for (box, general, tiles), chosen in zip(measured, plans.general_tiles([m[0] for m in measured])):
+        assert chosen == (general < tiles), box
