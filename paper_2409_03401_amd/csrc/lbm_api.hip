@@ -670,10 +670,9 @@ int lbm_step(lbm_handle* h, int64_t nsteps, void* stream) {
     }
     const int walls[2] = {h->base.wall_x, h->base.wall_y};
     // 3D with x or y walls: the general kernel bounces back there when it pulls, which saves
-    // the exchange after each step; on large grids of whole lines its plain stores cost more
-    // (128^3 FP32, closed: 191 us a step -> 165; 256^3: 1172 -> 1295)
+    // the exchange after each step
     const bool pull_xy = h->L.dim == 3 && nsteps > 1 && (walls[0] || walls[1]) &&
-                         (h->L.gen_steps || h->L.nodes < (1 << 22));
+                         (h->L.gen_steps || pull_walls(h->L.NX, h->L.nodes, h->L.qf, h->L.qs, walls[0] + walls[1]));
     const bool gen = h->L.gen_steps || pull_xy;
     for (int64_t i = 0; i < nsteps; ++i) {
         const int groups = launch_fused(h, MODE_STEP, gen, kp[h->cur], s);

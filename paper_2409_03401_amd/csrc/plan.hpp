@@ -39,6 +39,17 @@ constexpr bool general_tiles(int nx, long long nodes, int prec, int qf, int qs) 
     return lanes >= 1.2;
 }
 
+// 3D calls of several steps with x or y walls (`axes` of them), rows of whole lines and steps in
+// 64-wide tiles: does the general kernel, which bounces back there when it pulls, cost less than
+// an exchange after each step?  The exchange takes 10 to 50 us, the general kernel a share of a
+// step, most of it with flow on D3Q19 scalars and where its tiles are ragged.  Us a step, pulled /
+// exchanged: D3Q7 with flow FP32, closed, 128^3 170 / 193, 256^3 1304 / 1152, 288 x 96 x 64 152 / 164,
+// with x walls only 151 / 145; D3Q19 scalars with flow, x walls, 64^3 BF16 47 / 65, 160 x 96 x 80 FP64
+// 421 / 426, 128^3 FP64 670 / 622, BF16 279 / 263
+constexpr bool pull_walls(int nx, long long nodes, int qf, int qs, int axes) {
+    return nodes < (qf > 0 && qs == 19 ? 5 << 18 : qf > 0 && tile_lanes(nx) > 1.0 ? (axes > 1 ? 4 << 19 : 3 << 19) : 1 << 22);
+}
+
 // planes per work-group of the 3D kernels without the phi stencil, for `cols` columns of
 // tiles: one, two on large grids (96^3 FP64 step 67.2 -> 61.2 us, 256^3 FP32 580 -> 550 us
 // against the chunks of the other kernels); 0, those chunks, where the launch would be too

@@ -30,6 +30,10 @@ int main() {
             int nx, prec, qf;
             if (std::scanf("%d %lld %d %d %d", &nx, &n, &prec, &qf, &qs) != 5) return 1;
             std::printf("%d\n", int(general_tiles(nx, n, prec, qf, qs)));
+        } else if (what == 'p') {  // 3D calls with x or y walls: pulled?
+            int nx, qf, axes;
+            if (std::scanf("%d %lld %d %d %d", &nx, &n, &qf, &qs, &axes) != 5) return 1;
+            std::printf("%d\n", int(pull_walls(nx, n, qf, qs, axes)));
         } else if (what == 'n') {  // steps of a launch
             if (std::scanf("%lld %lld %lld", &n, &cols, &nz) != 3) return 1;
             std::printf("%lld\n", steps_of_launch(n, cols, nz));
@@ -91,6 +95,12 @@ def general_tiles(boxes):
     lines, go through the general kernel."""
     return [bool(r[0]) for r in _ask([f"g {nx} {nx * ny * nz} {PRECS[prec]} {qf} {qs}"
                                       for nx, ny, nz, prec, qf, qs in boxes])]
+
+
+def pull_walls(boxes):
+    """Whether calls of several steps of every (nx, ny, nz, fluid, scalar directions, axes with
+    walls among x and y) bounce back when they pull."""
+    return [bool(r[0]) for r in _ask([f"p {nx} {nx * ny * nz} {qf} {qs} {axes}" for nx, ny, nz, qf, qs, axes in boxes])]
 
 
 def steps_of_launch(launches):

@@ -129,3 +129,17 @@ def test_general_kernel_on_whole_rows():
     ]
     for (box, general, tiles), chosen in zip(measured, plans.general_tiles([m[0] for m in measured])):
         assert chosen == (general < tiles), box
+
+
+def test_walls_pulled_or_exchanged():
+    """3D boxes with walls and rows of whole lines, with us a step measured both ways."""
+    measured = [
+        ((128, 128, 128, 19, 7, 2), 170, 193), ((256, 256, 256, 19, 7, 2), 1304, 1152),
+        ((288, 96, 64, 19, 7, 2), 152, 164), ((288, 96, 64, 19, 7, 1), 151, 145),
+        ((224, 128, 128, 19, 7, 1), 325, 293), ((112, 112, 112, 19, 7, 1), 223, 228),
+        ((64, 64, 64, 19, 19, 1), 47, 65), ((128, 64, 32, 19, 19, 2), 62, 104), ((160, 96, 80, 19, 19, 1), 421, 426),
+        ((128, 128, 128, 19, 19, 1), 670, 622), ((224, 128, 128, 19, 19, 2), 1205, 1122),
+        ((288, 96, 64, 0, 7, 1), 58, 71), ((224, 128, 128, 0, 19, 1), 364, 383),
+    ]
+    for (box, pulled, exchanged), chosen in zip(measured, plans.pull_walls([m[0] for m in measured])):
+        assert chosen == (pulled < exchanged), box
