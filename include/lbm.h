@@ -191,10 +191,13 @@ typedef struct lbm_handle lbm_handle;
  * those reads would race with the neighbours' writes unless phi took a pass of
  * its own.  The cost is memory: twice the stored population bytes per node
  * (2 x 88 B with D3Q19 + 3 x D3Q7 and 16-bit storage, 23.8 GB for 512^3).
- * Tuning only: the environment variables LBM_TILE ("64x4" or "32x8" in 3D; "64x1",
- * "128x1" or "256x1" in 2D) and LBM_ZC (planes per work-group) override the launch
- * geometry the library chooses.  They are read whenever a configuration is checked,
- * so lbm_state_bytes and lbm_init must see the same values. */
+ * Tuning only: the environment variables LBM_TILE ("TXxTY" in 3D, up to 256 nodes whose ring of
+ * one node fits the work-group, e.g. "64x4" or "32x8"; "64x1", "128x1" or "256x1" in 2D) and LBM_ZC
+ * (planes per work-group) override the launch geometry the library chooses; values that do
+ * not fit are ignored.  Setting either also takes 2D runs one step per launch, sends every
+ * step through the kernel for general tiles, and drops the short chunks of the 3D kernels
+ * that need no phi stencil.  They are read whenever a configuration is checked, so
+ * lbm_state_bytes and lbm_init must see the same values. */
 int lbm_state_bytes(const lbm_config* cfg, size_t* bytes);
 int lbm_checkpoint_bytes(const lbm_config* cfg, size_t* bytes);
 

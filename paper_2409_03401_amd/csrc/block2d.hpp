@@ -22,11 +22,12 @@
 // window takes about 0.5 us a step without flow, 1 us with), on large ones the memory
 // traffic, 1 / nsub of the marching kernel's times the share of the windows that overlaps.
 // Measured, us per step, marching kernel -> windows:
-//   512 x 1   D2Q5 FP64, walls in x       8.3 -> 0.66 (four windows, 67 steps per launch)
+//   512 x 1   D2Q5 FP64, walls in x       8.3 -> 0.65 (nine windows, 100 steps per launch)
 //   150 x 93  D2Q9 + 3 x D2Q5 FP32, walls 14.9 -> 2.7 (16 x 16 windows)
-//   512^2     D2Q9 + 3 x D2Q5 FP32        14.9 -> 8.9
-//   1024^2    3 x D2Q5 FP32               26.3 -> 10.9
+//   512^2     D2Q9 + 3 x D2Q5 FP32        14.9 -> 9.0
+//   1024^2    3 x D2Q5 FP32               26.3 -> 10.8
 //   4096^2    3 x D2Q9 BF16                430 -> 266
+// Which windows run, how many steps each and whether any do is the plan's choice (plan.hpp).
 #pragma once
 
 #include "node.hpp"

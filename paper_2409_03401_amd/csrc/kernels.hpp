@@ -134,8 +134,11 @@ constexpr int lbm_waves() {
 // GEN: any grid.  3D: the tile is P.tile_x x P.tile_y nodes, and a source copy with raw
 // populations at the x and y walls (P.raw_xy) bounces back there; stores are plain.
 // Otherwise 64 x 4 tiles (3D), exchanged copies, and non-temporal stores: the grids whose
-// rows are whole 128-byte lines.  The general kernel spends 20-60 scalar registers more
-// (spilled to vector lanes), 2-6 % on such a grid.
+// rows are whole 128-byte lines.  The general kernel spills more scalar registers: on D3Q7 with
+// flow 83 against 31 in FP32 and 98 against 39 in FP64, to vector lanes (2-6 % on such a grid);
+// on D3Q19 scalars 370 against 56 and 422 against 70, with 72 and 68 bytes of scratch memory,
+// most of them for the x and y walls of raw copies (224 x 128 x 128 FP32, which has none, 647 us a
+// step against 530).  Which grids take it: general_tiles, pull_walls (plan.hpp).
 template <class SL, class FL, int MODE, int PREC, int NT, bool GEN, int COLL = COLL_BGK, int NC = 2>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(lbm_waves<SL, PREC, COLL, NC, FL::Q>())))
 k_lbm(const KParams P) {
