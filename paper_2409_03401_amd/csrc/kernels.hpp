@@ -106,7 +106,8 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[N], int maxslot, 
 // - 2D with 16-bit storage and flow, kernels of 129-146 registers (three waves): four
 //   waves per SIMD measured at 2048^2 +9-13 % with a third composition, +13-14 % for the
 //   variable-density model on D2Q9 scalars, +14 % for the paper's D2Q9 lattices with
-//   FP16, +8 % for MRT on D2Q5 with BF16;
+//   FP16, +8 % for MRT on D2Q5 with BF16; general curvatures on D2Q5 need 127-135 registers:
+//   2048^2 FP16 126 us a step against 147, 1500 x 700 BF16 in single steps 42.7 against 44.4;
 // - the D3Q19 scalar lattices with flow in FP32, whose one-plane LDS ring lets two
 //   work-groups share a compute unit (128^3: 294 us a step; 310 at one wave with the next
 //   plane in registers).
@@ -127,6 +128,7 @@ constexpr int lbm_waves() {
         if constexpr (SL::Q == 9 && COLL == COLL_VD) return 4;
         if constexpr (SL::Q == 9 && COLL == COLL_BGK && PREC == P16) return 4;
         if constexpr (SL::Q == 5 && COLL == COLL_MRT && PREC == PB16) return 4;
+        if constexpr (SL::Q == 5 && COLL == COLL_GK) return 4;
     }
     return LBM_WAVES_PER_EU;
 }
