@@ -176,8 +176,9 @@ k_lbm(const KParams P) {
     constexpr bool S16 = PREC == P16 || PREC == PB16;
     // wall planes replace their bounced populations after the common loads instead of taking a
     // copy of the whole fill: in the general kernel, and where the copy crowds the registers
-    // (128^3 D3Q19 scalars BF16 210 us a step against 230)
-    constexpr bool REPL = GEN || (S16 && QS == 19);
+    // (128^3 D3Q19 scalars BF16 210 us a step against 230).  The variable-density model in FP16
+    // keeps the copy (256^3 D3Q19 scalars 1720 us a step, 1770 with the replacement)
+    constexpr bool REPL = GEN || (S16 && QS == 19 && !(VD && PREC == P16));
     constexpr bool INPLACE = HAS_Y && STENCIL && !S16 && 2 * PLANE > 64 * 1024 && PLANE <= 64 * 1024;
     constexpr bool LDS_POPS = LBM_LDS_POPS && (INPLACE || lbm_waves<SL, PREC, COLL, NC, FL::Q>() == 2 ||
                                                2 * PLANE <= 96 * 1024);
